@@ -224,6 +224,52 @@ int run_blocks(qs_state *h, const qs_program_t *p, int b0, int b1)
     return QS_OK;
 }
 
+// The program's tile plan: passes, and gates of their own by their blocks.
+int run_steps(qs_state *h, const qs_program_t *p)
+{
+    for (size_t i = 0; i < p->tiles.steps.size(); ++i) {
+        const TileStep &s = p->tiles.steps[i];
+        const int rc = s.pass >= 0 ? launch_tile_pass(h, p->tiles.passes[size_t(s.pass)], p->dwords)
+                                   : run_blocks(h, p, p->alone[i], p->alone[i] + 1);
+        if (rc) return rc;
+    }
+    return QS_OK;
+}
+
+// Arguments of qs_compile and qs_apply_circuit.
+int check_circuit(const qs_state *h, const qs_circuit *c, int max_k)
+{
+    if (max_k < 1 || max_k > QS_MAX_K) return fail(QS_EINVAL, "max_k=%d outside [1, %d]", max_k, QS_MAX_K);
+    if (int rc = validate_circuit(c, h->n)) return rc;
+    for (int g = 0; g < c->n_gates; ++g) {
+        const uint64_t cm = c->ctrl_mask ? c->ctrl_mask[g] : 0;
+        if (c->k[g] + __builtin_popcountll(cm) > QS_MAX_K)
+            return fail(QS_EUNSUPPORTED, "gate %d spans more than %d qubits with its controls", g, QS_MAX_K);
+    }
+    return QS_OK;
+}
+
+// Estimated time of a plan's blocks, in sweeps. A block of diagonal gates
+// sweeps only what it changes, a quarter of the state for a CZ.
+double blocks_cost(const qs_state *h, const qs_circuit *c, const Plan &p)
+{
+    std::vector<char> diag(size_t(std::max(0, c->n_gates)));
+    const double *m = c->matrices;
+    for (int g = 0; g < c->n_gates; ++g) {
+        GateDesc d;
+        classify(m, c->k[g], d);
+        diag[size_t(g)] = d.cls == GC_IDENTITY || d.cls == GC_PHASE1 || d.cls == GC_DIAG;
+        m += size_t(2) << (2 * c->k[g]);
+    }
+    double cost = 0;
+    for (size_t b = 0; b < p.block_gates.size(); ++b) {
+        bool all = true;
+        for (int g : p.block_gates[b]) all = all && diag[size_t(g)];
+        cost += all ? 0.25 : dense_cost(h->amp_bytes(), int(p.block_qubits[b].size()));
+    }
+    return cost;
+}
+
 }  // namespace
 
 extern "C" {
@@ -439,13 +485,7 @@ int qs_compile(qs_handle h, const qs_circuit *c, int max_k, qs_program *out)
     if (int rc = check_handle(h)) return rc;
     if (!out) return fail(QS_EINVAL, "NULL output program");
     *out = nullptr;
-    if (max_k < 1 || max_k > QS_MAX_K) return fail(QS_EINVAL, "max_k=%d outside [1, %d]", max_k, QS_MAX_K);
-    if (int rc = validate_circuit(c, h->n)) return rc;
-    for (int g = 0; g < c->n_gates; ++g) {
-        const uint64_t cm = c->ctrl_mask ? c->ctrl_mask[g] : 0;
-        if (c->k[g] + __builtin_popcountll(cm) > QS_MAX_K)
-            return fail(QS_EUNSUPPORTED, "gate %d spans more than %d qubits with its controls", g, QS_MAX_K);
-    }
+    if (int rc = check_circuit(h, c, max_k)) return rc;
     Plan p;
     if (int rc = plan_fusion(h->n, c->n_gates, c->k, c->targets, c->ctrl_mask, max_k, p, far_qubit(h->amp_bytes())))
         return rc;
@@ -465,7 +505,29 @@ int qs_compile(qs_handle h, const qs_circuit *c, int max_k, qs_program *out)
     std::vector<double> gm;
     int kmax = 1;
     int64_t out_off = 0;
-    for (int b = 0; b < pr->n_blocks; ++b) {
+    // Programs of up to 13 qubits (two tiles) always run by their blocks: on
+    // such states a run in ranges gives the bits of one whole run.
+    pr->tiled = h->n > 13 && plan_tiles(h->n, h->amp_bytes(), c, pr->tiles) && pr->tiles.cost < blocks_cost(h, c, p);
+    int n_composed = pr->n_blocks;
+    if (pr->tiled) {
+        // gates that the passes leave out are composed behind the blocks
+        pr->alone.assign(pr->tiles.steps.size(), -1);
+        for (size_t i = 0; i < pr->tiles.steps.size(); ++i) {
+            const int g = pr->tiles.steps[i].gate;
+            if (g < 0) continue;
+            std::vector<int> q(c->targets + toff[size_t(g)], c->targets + toff[size_t(g) + 1]);
+            const uint64_t cm = c->ctrl_mask ? c->ctrl_mask[g] : 0;
+            for (int b = 0; b < 64; ++b)
+                if ((cm >> b) & 1) q.push_back(b);
+            std::sort(q.begin(), q.end());
+            p.block_gates.push_back({g});
+            p.block_qubits.push_back(q);
+            pr->alone[i] = n_composed++;
+        }
+    } else {
+        pr->tiles = TilePlan();
+    }
+    for (int b = 0; b < n_composed; ++b) {
         const auto &qs = p.block_qubits[size_t(b)];
         const int kb = int(qs.size());
         kmax = std::max(kmax, kb);
@@ -517,10 +579,18 @@ int qs_compile(qs_handle h, const qs_circuit *c, int max_k, qs_program *out)
         cleanup();
         if (pr->dmats) (void)hipFree(pr->dmats);
         if (pr->dmats32) (void)hipFree(pr->dmats32);
+        if (pr->dwords) (void)hipFree(pr->dwords);
         delete pr;
         return r;
     };
-    if (pr->n_blocks > 0) {
+    if (pr->tiled) {
+        const size_t bytes = pr->tiles.words.size() * sizeof(uint64_t);
+        hipError_t e = hipMalloc(reinterpret_cast<void **>(&pr->dwords), bytes);
+        if (e == hipSuccess) e = hipMemcpy(pr->dwords, pr->tiles.words.data(), bytes, hipMemcpyHostToDevice);
+        if (e != hipSuccess) return bail(hip_fail(e, "program words"));
+        pr->tiles.words = {};
+    }
+    if (n_composed > 0) {
         hipError_t e = hipSuccess;
         if ((e = hipMalloc(&dcg, sizeof(ComposeGate) * cg.size())) != hipSuccess ||
             (e = hipMalloc(&dcb, sizeof(ComposeBlock) * cb.size())) != hipSuccess ||
@@ -532,7 +602,7 @@ int qs_compile(qs_handle h, const qs_circuit *c, int max_k, qs_program *out)
             (e = hipMemcpyAsync(dcb, cb.data(), sizeof(ComposeBlock) * cb.size(), hipMemcpyHostToDevice, h->stream)) != hipSuccess ||
             (e = hipMemcpyAsync(dgm, gm.data(), sizeof(double) * gm.size(), hipMemcpyHostToDevice, h->stream)) != hipSuccess)
             return bail(hip_fail(e, "hipMemcpyAsync(program)"));
-        if ((rc = launch_compose(h->stream, pr->n_blocks, static_cast<ComposeBlock *>(dcb),
+        if ((rc = launch_compose(h->stream, n_composed, static_cast<ComposeBlock *>(dcb),
                                  static_cast<ComposeGate *>(dcg), static_cast<double *>(dgm),
                                  pr->dmats, kmax)))
             return bail(rc);
@@ -601,6 +671,7 @@ int qs_run_program_range(qs_handle h, qs_program p, int b0, int b1)
     if (p->n != h->n) return fail(QS_EINVAL, "program built for %d qubits, state has %d", p->n, h->n);
     if (b0 < 0 || b1 < b0 || b1 > p->n_blocks)
         return fail(QS_EINVAL, "block range [%d, %d) outside [0, %d]", b0, b1, p->n_blocks);
+    if (p->tiled && b0 == 0 && b1 == p->n_blocks) return run_steps(h, p);
     return run_blocks(h, p, b0, b1);
 }
 
@@ -626,14 +697,15 @@ int qs_run_program(qs_handle h, qs_program p)
     if (int rc = check_handle(h)) return rc;
     if (!p) return fail(QS_EINVAL, "NULL program");
     if (p->n != h->n) return fail(QS_EINVAL, "program built for %d qubits, state has %d", p->n, h->n);
-    return run_blocks(h, p, 0, p->n_blocks);
+    return p->tiled ? run_steps(h, p) : run_blocks(h, p, 0, p->n_blocks);
 }
 
 int qs_program_free(qs_program p)
 {
     clear_error();
     if (!p) return QS_OK;
-    if (p->dmats || p->dmats32) (void)hipDeviceSynchronize();
+    if (p->dmats || p->dmats32 || p->dwords) (void)hipDeviceSynchronize();
+    if (p->dwords) (void)hipFree(p->dwords);
     if (p->dmats) (void)hipFree(p->dmats);
     if (p->dmats32) (void)hipFree(p->dmats32);
     delete p;
@@ -642,6 +714,27 @@ int qs_program_free(qs_program p)
 
 int qs_apply_circuit(qs_handle h, const qs_circuit *c, int max_k)
 {
+    clear_error();
+    if (int rc = check_handle(h)) return rc;
+    if (int rc = check_circuit(h, c, max_k)) return rc;
+    // Passes need no composed blocks: their words go through the staging
+    // ring and nothing is allocated. A plan with gates of their own, which
+    // would stage matrices over the words, is compiled.
+    TilePlan t;
+    const bool planned = plan_tiles(h->n, h->amp_bytes(), c, t) && t.steps.size() == t.passes.size() &&
+                         !t.steps.empty() && t.words.size() * sizeof(uint64_t) <= h->stage.cap;
+    if (planned) {
+        Plan pl;
+        if (int rc = plan_fusion(h->n, c->n_gates, c->k, c->targets, c->ctrl_mask, max_k, pl, far_qubit(h->amp_bytes())))
+            return rc;
+        if (t.cost < blocks_cost(h, c, pl)) {
+            void *dw = nullptr;
+            if (int rc = h->stage.put(h->stream, t.words.data(), t.words.size() * sizeof(uint64_t), &dw)) return rc;
+            for (const TilePass &ps : t.passes)
+                if (int rc = launch_tile_pass(h, ps, static_cast<const uint64_t *>(dw))) return rc;
+            return QS_OK;
+        }
+    }
     qs_program p = nullptr;
     if (int rc = qs_compile(h, c, max_k, &p)) return rc;
     int rc = qs_run_program(h, p);

@@ -1,0 +1,523 @@
+// Planner of the tile passes (host only; kernel in tile.hip).
+//
+// Two levels. A pass takes T qubits of the state (the lowest ones always
+// among them) and every gate that can be applied while only those are at
+// hand; a stage of the pass takes four of them (the register qubits) and
+// every gate of the pass that needs no others. Both levels scan the gates
+// left in circuit order: a gate is taken if the qubits it needs are there and
+// it commutes with every gate skipped so far. Two gates commute when on each
+// qubit they share both are diagonal, as controls, phases and CZ are.
+//
+// A gate needs at hand only the qubits it is not diagonal on. Diagonal gates
+// need none: their phases wait as terms (index mask, index values, phase)
+// and are applied just before the next gate that does not commute with them,
+// when one of their qubits is a register qubit anyway.
+#include "tile.h"
+
+#include <algorithm>
+#include <cstring>
+
+#include "qs_internal.h"
+
+namespace qs {
+namespace {
+
+enum Kind { kOne, kTwo, kSwap, kDiagonal, kAlone, kNothing };
+
+struct TGate {
+    int kind = kAlone;
+    bool x = false;            // kOne: exactly X
+    uint64_t need = 0;         // qubits the gate is not diagonal on
+    uint64_t diag = 0;         // qubits it is diagonal on
+    uint64_t cvals = 0;        // kOne: control values (mask: diag)
+    int target[2] = {0, 0};    // kOne, kTwo
+    double m[8] = {0};         // kOne
+    const double *mat = nullptr;
+    const int *targets = nullptr;
+    int k = 0;
+    uint64_t cmask = 0, cv = 0;
+};
+
+struct Term {
+    uint64_t mask, vals;
+    double pr, pi;
+};
+
+uint64_t word_of(double v)
+{
+    uint64_t w;
+    std::memcpy(&w, &v, sizeof w);
+    return w;
+}
+
+// A two-qubit matrix that is a one-qubit gate under a control (CNOT or CZ
+// given as a 4 x 4 matrix): control bit t of the local index, value v, acts
+// as the 2 x 2 matrix on the other bit and as the identity where the control
+// differs.
+bool as_controlled(const double *m, int &ctrl, int &val, double *u)
+{
+    auto at = [&](int r, int c) { return m + 2 * (4 * r + c); };
+    for (ctrl = 0; ctrl < 2; ++ctrl)
+        for (val = 0; val < 2; ++val) {
+            bool ok = true;
+            for (int r = 0; r < 4 && ok; ++r)
+                for (int c = 0; c < 4 && ok; ++c) {
+                    const int rb = (r >> ctrl) & 1, cb = (c >> ctrl) & 1;
+                    const double *e = at(r, c);
+                    if (rb != cb) ok = e[0] == 0.0 && e[1] == 0.0;
+                    else if (rb != val) ok = e[0] == (r == c ? 1.0 : 0.0) && e[1] == 0.0;
+                }
+            if (!ok) continue;
+            for (int r = 0; r < 2; ++r)
+                for (int c = 0; c < 2; ++c) {
+                    const int o = 1 - ctrl;
+                    const double *e = at((val << ctrl) | (r << o), (val << ctrl) | (c << o));
+                    u[2 * (2 * r + c)] = e[0];
+                    u[2 * (2 * r + c) + 1] = e[1];
+                }
+            return true;
+        }
+    return false;
+}
+
+void read_gate(int k, const int *targets, const double *m, uint64_t cmask, uint64_t cvals, TGate &g)
+{
+    GateDesc d;
+    classify(m, k, d);
+    uint64_t tm = 0;
+    for (int i = 0; i < k; ++i) tm |= 1ull << targets[i];
+    g.mat = m;
+    g.targets = targets;
+    g.k = k;
+    g.cmask = cmask;
+    g.cv = cvals;
+    if (d.cls == GC_IDENTITY) {
+        g.kind = kNothing;
+        return;
+    }
+    if (d.cls == GC_PHASE1 || d.cls == GC_DIAG) {
+        g.kind = kDiagonal;
+        g.diag = tm | cmask;
+        return;
+    }
+    g.need = tm;
+    g.diag = cmask;
+    g.cvals = cvals;
+    if (k == 1) {
+        g.kind = kOne;
+        g.target[0] = targets[0];
+        std::copy_n(m, 8, g.m);
+    } else if (k == 2 && cmask == 0) {
+        int ctrl, val;
+        g.target[0] = targets[0];
+        g.target[1] = targets[1];
+        if (as_controlled(m, ctrl, val, g.m)) {
+            g.kind = kOne;
+            g.target[0] = targets[1 - ctrl];
+            g.need = 1ull << targets[1 - ctrl];
+            g.diag = 1ull << targets[ctrl];
+            g.cvals = val ? g.diag : 0;
+        } else {
+            static const double sw[32] = {1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 1, 0, 0, 0,
+                                          0, 0, 1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 1, 0};
+            g.kind = std::equal(m, m + 32, sw) ? kSwap : kTwo;
+        }
+    }
+    if (g.kind == kOne) {
+        static const double xm[8] = {0, 0, 1, 0, 1, 0, 0, 0};
+        g.x = std::equal(g.m, g.m + 8, xm);
+    }
+}
+
+void add_terms(const TGate &g, std::vector<Term> &out)
+{
+    const int D = 1 << g.k;
+    uint64_t tm = 0;
+    for (int i = 0; i < g.k; ++i) tm |= 1ull << g.targets[i];
+    for (int j = 0; j < D; ++j) {
+        const double pr = g.mat[2 * (size_t(j) * D + j)], pi = g.mat[2 * (size_t(j) * D + j) + 1];
+        if (pr == 1.0 && pi == 0.0) continue;
+        uint64_t v = g.cv;
+        for (int i = 0; i < g.k; ++i)
+            if ((j >> i) & 1) v |= 1ull << g.targets[i];
+        out.push_back(Term{tm | g.cmask, v, pr, pi});
+    }
+}
+
+// Qubits of the gates skipped so far, by how those gates act on them.
+struct Skipped {
+    uint64_t diag = 0, other = 0;
+    bool blocks(const TGate &g) const { return (g.need & (diag | other)) || (g.diag & other); }
+    void add(const TGate &g)
+    {
+        diag |= g.diag;
+        other |= g.need;
+    }
+};
+
+int bits(uint64_t m) { return __builtin_popcountll(m); }
+
+struct Planner {
+    int n, T, low;                 // low: qubits inside a 128-byte line
+    const std::vector<TGate> &gates;
+    TilePlan &out;
+    std::vector<Term> pending;
+    double flops = 0;              // multiply-adds per amplitude
+
+    Planner(int n_, int T_, int low_, const std::vector<TGate> &g, TilePlan &o) : n(n_), T(T_), low(low_), gates(g), out(o) {}
+
+    // Gates of `left` that a pass with tile `S` takes; grow: take qubits of
+    // skipped gates into S while there is room.
+    double closure(const std::vector<int> &left, uint64_t &S, bool grow, std::vector<int> *ex) const
+    {
+        const uint64_t all = (n >= 64 ? 0 : (1ull << n)) - 1;
+        Skipped sk;
+        double score = 0;
+        for (int i : left) {
+            const TGate &g = gates[size_t(i)];
+            bool take = false;
+            if (!sk.blocks(g) && g.kind != kAlone) {
+                if (!(g.need & ~S)) take = true;
+                else if (grow && bits(S | g.need) <= T) {
+                    S |= g.need;
+                    take = true;
+                }
+            }
+            if (take) {
+                score += g.need ? 1.0 : 0.3;
+                if (ex) ex->push_back(i);
+            } else {
+                sk.add(g);
+                if (sk.other == all) break;
+            }
+        }
+        return score;
+    }
+
+    // The tile that takes most gates, grown by one frontier gate's qubits at
+    // a time. About a fifth fewer passes than taking qubits in circuit
+    // order, for some ten times the planning.
+    uint64_t best_tile(const std::vector<int> &left, uint64_t S) const
+    {
+        while (bits(S) < T) {
+            const double now = closure(left, S, false, nullptr);
+            std::vector<uint64_t> cand;
+            Skipped sk;
+            for (int i : left) {
+                const TGate &g = gates[size_t(i)];
+                const bool free = !sk.blocks(g) && g.kind != kAlone;
+                if (free && !(g.need & ~S)) continue;
+                if (free && bits(S | g.need) <= T) {
+                    const uint64_t a = g.need & ~S;
+                    if (std::find(cand.begin(), cand.end(), a) == cand.end()) cand.push_back(a);
+                }
+                sk.add(g);
+            }
+            uint64_t pick = 0;
+            double best = -1;
+            for (uint64_t a : cand) {
+                uint64_t s = S | a;
+                const double gain = (closure(left, s, false, nullptr) - now) / bits(a);
+                if (gain > best) {
+                    best = gain;
+                    pick = a;
+                }
+            }
+            if (!pick) break;
+            S |= pick;
+        }
+        return S;
+    }
+
+    // ----- stages ---------------------------------------------------------
+    struct Stage {
+        uint64_t regs = 0;
+        std::vector<int> gates;
+    };
+
+    // The tile's bits as a stage lays them out: thread bits, then registers.
+    void layout(const TilePass &p, uint64_t regs, std::vector<uint64_t> &w, int *reg_bit) const
+    {
+        std::vector<int> thr, reg;
+        for (int i = 0; i < T; ++i) ((regs >> p.pos[i]) & 1 ? reg : thr).push_back(i);
+        // the low five lane bits on tile bits that differ modulo 5, lowest first
+        std::vector<int> order;
+        uint32_t cls = 0;
+        for (int t : thr)
+            if (!((cls >> (t % 5)) & 1) && order.size() < 5) {
+                cls |= 1u << (t % 5);
+                order.push_back(t);
+            }
+        for (int t : thr)
+            if (std::find(order.begin(), order.end(), t) == order.end()) order.push_back(t);
+        uint64_t w0 = 0, w1 = 0, w2 = 0;
+        for (int i = 0; i < T - 4; ++i) {
+            w0 |= uint64_t(order[size_t(i)]) << (4 * i);
+            w1 |= uint64_t(p.pos[order[size_t(i)]]) << (6 * i);
+        }
+        for (int b = 0; b < 4; ++b) {
+            w0 |= uint64_t(reg[size_t(b)]) << (4 * (T - 4 + b));
+            w2 |= uint64_t(p.pos[reg[size_t(b)]]) << (6 * b);
+            reg_bit[b] = p.pos[reg[size_t(b)]];
+        }
+        w.push_back(w0);
+        w.push_back(w1);
+        w.push_back(w2);
+    }
+
+    // Register mask of the registers whose bits match (mask, vals); the part
+    // of both outside the registers is left in omask, ovals.
+    static uint32_t registers(const int *reg_bit, uint64_t mask, uint64_t vals, uint64_t &omask, uint64_t &ovals)
+    {
+        uint32_t amps = 0;
+        for (int j = 0; j < 16; ++j) {
+            bool on = true;
+            for (int b = 0; b < 4; ++b)
+                if ((mask >> reg_bit[b]) & 1) on = on && ((vals >> reg_bit[b]) & 1) == uint64_t((j >> b) & 1);
+            if (on) amps |= 1u << j;
+        }
+        uint64_t r = 0;
+        for (int b = 0; b < 4; ++b) r |= 1ull << reg_bit[b];
+        omask = mask & ~r;
+        ovals = vals & ~r;
+        return amps;
+    }
+
+    // Applies the waiting terms that involve a qubit of `which` here.
+    int flush(uint64_t which, const int *reg_bit, std::vector<uint64_t> &w)
+    {
+        std::vector<Term> keep, now;
+        for (const Term &t : pending) ((t.mask & which) ? now : keep).push_back(t);
+        if (now.empty()) return 0;
+        pending.swap(keep);
+        struct Placed {
+            uint32_t amps;
+            uint64_t om, ov;
+            double pr, pi;
+        };
+        std::vector<Placed> sign, ph;
+        uint32_t any = 0;
+        for (const Term &t : now) {
+            Placed q;
+            q.amps = registers(reg_bit, t.mask, t.vals, q.om, q.ov);
+            q.pr = t.pr;
+            q.pi = t.pi;
+            if (t.pr == -1.0 && t.pi == 0.0) {
+                sign.push_back(q);
+                any |= q.amps;
+            } else {
+                ph.push_back(q);
+            }
+        }
+        int ops = 0;
+        size_t s = 0;
+        std::stable_sort(ph.begin(), ph.end(), [](const Placed &a, const Placed &b) { return a.amps < b.amps; });
+        const size_t head = w.size();
+        w.push_back(0);
+        const uint64_t ns = std::min<size_t>(sign.size(), 0xffff);
+        for (; s < ns; ++s) {
+            w.push_back(sign[s].om);
+            w.push_back(sign[s].ov);
+            w.push_back(sign[s].amps);
+        }
+        for (; s < sign.size(); ++s) ph.push_back(sign[s]);   // past the count's range
+        uint64_t groups = 0;
+        for (size_t i = 0; i < ph.size();) {
+            size_t e = i;
+            while (e < ph.size() && ph[e].amps == ph[i].amps) ++e;
+            w.push_back(uint64_t(ph[i].amps) | uint64_t(e - i) << 16);
+            for (size_t j = i; j < e; ++j) {
+                w.push_back(ph[j].om);
+                w.push_back(ph[j].ov);
+                w.push_back(word_of(ph[j].pr));
+                w.push_back(word_of(ph[j].pi));
+            }
+            ++groups;
+            flops += 4.0 * bits(ph[i].amps) / 16.0 + (e - i);
+            i = e;
+        }
+        flops += ns ? 2.0 + 0.25 * double(ns) : 0.0;
+        w[head] = uint64_t(kTileDiag) | ns << 8 | groups << 24 | uint64_t(any) << 40;
+        ++ops;
+        return ops;
+    }
+
+    static int reg_of(const int *reg_bit, int q)
+    {
+        for (int b = 0; b < 4; ++b)
+            if (reg_bit[b] == q) return b;
+        return -1;
+    }
+
+    int emit_gate(const TGate &g, const int *reg_bit, std::vector<uint64_t> &w)
+    {
+        if (g.kind == kOne) {
+            const uint64_t b = uint64_t(reg_of(reg_bit, g.target[0]));
+            if (!g.diag && !g.x) {
+                w.push_back(uint64_t(kTileDense1) | b << 8);
+                for (int i = 0; i < 8; ++i) w.push_back(word_of(g.m[i]));
+                flops += 8;
+                return 1;
+            }
+            uint64_t om, ov;
+            const uint32_t amps = registers(reg_bit, g.diag, g.cvals, om, ov);
+            w.push_back(uint64_t(g.x ? kTileX : kTileCDense1) | b << 8 | uint64_t(amps) << 16);
+            w.push_back(om);
+            w.push_back(ov);
+            if (!g.x)
+                for (int i = 0; i < 8; ++i) w.push_back(word_of(g.m[i]));
+            flops += g.x ? 2 : 8;
+            return 1;
+        }
+        const int a = reg_of(reg_bit, g.target[0]), b = reg_of(reg_bit, g.target[1]);
+        const int lo = std::min(a, b), hi = std::max(a, b);
+        static const int pair_no[4][4] = {{0, 0, 1, 2}, {0, 0, 3, 4}, {0, 0, 0, 5}, {0, 0, 0, 0}};
+        const uint64_t q = uint64_t(pair_no[lo][hi]);
+        if (g.kind == kSwap) {
+            w.push_back(uint64_t(kTileSwap) | q << 8);
+            flops += 2;
+            return 1;
+        }
+        w.push_back(uint64_t(kTileDense2) | q << 8);
+        auto loc = [&](int i) { return a < b ? i : ((i & 1) << 1) | (i >> 1); };   // local bit 0 = lower register
+        for (int r = 0; r < 4; ++r)
+            for (int c = 0; c < 4; ++c) {
+                const double *e = g.mat + 2 * (4 * loc(r) + loc(c));
+                w.push_back(word_of(e[0]));
+                w.push_back(word_of(e[1]));
+            }
+        flops += 18;
+        return 1;
+    }
+
+    // One pass over the gates ex (in order); last: apply every waiting term.
+    void pass(uint64_t S, const std::vector<int> &ex, bool last)
+    {
+        const uint64_t lowmask = (1ull << low) - 1;
+        for (int q = 0; bits(S) < T; ++q) S |= 1ull << q;   // room left: near qubits
+        TilePass p;
+        p.T = T;
+        for (int q = 0, c = 0; q < n; ++q)
+            if ((S >> q) & 1) p.pos[c++] = q;
+        p.word0 = out.words.size();
+        // stages; the first and the last keep the line qubits on the lanes,
+        // so that global accesses move whole lines
+        std::vector<Stage> st;
+        std::vector<int> left = ex;
+        while (!left.empty()) {
+            Stage s;
+            Skipped sk;
+            std::vector<int> rest;
+            for (int i : left) {
+                const TGate &g = gates[size_t(i)];
+                bool take = !sk.blocks(g);
+                if (take && g.need & ~s.regs) {
+                    take = bits(s.regs | g.need) <= 4 && !(st.empty() && (g.need & lowmask));
+                    if (take) s.regs |= g.need;
+                }
+                if (take) s.gates.push_back(i);
+                else {
+                    sk.add(g);
+                    rest.push_back(i);
+                }
+            }
+            left.swap(rest);
+            st.push_back(s);
+        }
+        if (st.empty() || (st.back().regs & lowmask)) st.push_back(Stage());
+        for (size_t si = 0; si < st.size(); ++si) {
+            Stage &s = st[si];
+            // free register places: high tile bits, where lanes and lines are not
+            for (int i = T - 1; bits(s.regs) < 4; --i)
+                if (!((s.regs >> p.pos[i]) & 1)) s.regs |= 1ull << p.pos[i];
+            int reg_bit[4];
+            layout(p, s.regs, out.words, reg_bit);
+            const size_t head = out.words.size() - 1;
+            uint64_t ops = 0;
+            for (int gi : s.gates) {
+                const TGate &g = gates[size_t(gi)];
+                if (g.kind == kDiagonal) {
+                    add_terms(g, pending);
+                    continue;
+                }
+                bool clash = false;
+                for (const Term &t : pending) clash = clash || (t.mask & g.need);
+                if (clash) ops += uint64_t(flush(s.regs, reg_bit, out.words));
+                ops += uint64_t(emit_gate(g, reg_bit, out.words));
+            }
+            if (last && si + 1 == st.size()) ops += uint64_t(flush(~0ull, reg_bit, out.words));
+            out.words[head] |= ops << 32;
+        }
+        p.n_stages = int(st.size());
+        TileStep step;
+        step.pass = int(out.passes.size());
+        out.passes.push_back(p);
+        out.steps.push_back(step);
+    }
+};
+
+}  // namespace
+
+// Time of a dense sweep of a k-qubit block, in sweeps limited by memory
+// alone (30 qubits, complex128: 5.7 ms for k <= 4, 6.6 and 21.3 ms for k = 5
+// and 6; complex64: 2.9, 3.5 and 4.5 ms).
+double dense_cost(size_t amp_bytes, int k)
+{
+    if (k <= 4) return 1.0;
+    if (amp_bytes == 16) return k == 5 ? 1.2 : 3.7;
+    return k == 5 ? 1.2 : 1.55;
+}
+
+bool plan_tiles(int n, size_t amp_bytes, const qs_circuit *c, TilePlan &out)
+{
+    out = TilePlan();
+    if (n < kTileBitsMin) return false;
+    const int T = std::min(n, 12), low = amp_bytes == 16 ? 3 : 4;
+    std::vector<TGate> gates(size_t(std::max(0, c->n_gates)));
+    const int *tp = c->targets;
+    const double *mp = c->matrices;
+    std::vector<int> left;
+    for (int g = 0; g < c->n_gates; ++g) {
+        const uint64_t cm = c->ctrl_mask ? c->ctrl_mask[g] : 0;
+        read_gate(c->k[g], tp, mp, cm, c->ctrl_vals ? c->ctrl_vals[g] & cm : 0, gates[size_t(g)]);
+        tp += c->k[g];
+        mp += size_t(2) << (2 * c->k[g]);
+        if (gates[size_t(g)].kind != kNothing) left.push_back(g);
+    }
+    Planner pl(n, T, low, gates, out);
+    const uint64_t lowmask = (1ull << low) - 1;
+    // Searching for tiles costs a millisecond for some hundred gates and
+    // saves two or three passes: worth it once a pass takes as long.
+    const bool search = (amp_bytes << n) >= (size_t(1) << 29);
+    std::vector<char> done(gates.size(), 0);
+    while (!left.empty()) {
+        if (gates[size_t(left[0])].kind == kAlone) {
+            TileStep s;
+            s.gate = left[0];
+            out.steps.push_back(s);
+            left.erase(left.begin());
+            continue;
+        }
+        uint64_t S = lowmask;
+        if (search) S = pl.best_tile(left, S);
+        std::vector<int> ex;
+        pl.closure(left, S, true, &ex);
+        for (int i : ex) done[size_t(i)] = 1;
+        std::vector<int> rest;
+        for (int i : left)
+            if (!done[size_t(i)]) rest.push_back(i);
+        left.swap(rest);
+        pl.pass(S, ex, left.empty() || gates[size_t(left[0])].kind == kAlone);
+    }
+    // Estimated time in sweeps: a pass moves the state as a sweep does, with
+    // longer strides, and its multiply-adds hide behind the memory in part
+    // (30 TFMA/s against 6 TB/s); an unfused gate on up to four qubits is a
+    // sweep.
+    const double fma = (30e12 / 6e12) * 2.0 * double(amp_bytes);
+    out.cost = 1.2 * double(out.passes.size()) + 0.8 * pl.flops / fma;
+    for (const TileStep &s : out.steps)
+        if (s.gate >= 0) out.cost += dense_cost(amp_bytes, c->k[s.gate]);
+    return true;
+}
+
+}  // namespace qs

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "qs.h"
+#include "tile.h"
 
 namespace qs {
 
@@ -205,4 +206,11 @@ struct qs_program_t {
     float *dmats32 = nullptr;            // FP32 copies (device)
     size_t mats_doubles = 0;
     int device = 0;
+    // The whole program as passes over tiles, where that is estimated to be
+    // faster than its blocks; alone[i] is the composed block (at or past
+    // n_blocks) of the plan's step i when that is a gate of its own.
+    bool tiled = false;
+    qs::TilePlan tiles;
+    std::vector<int> alone;
+    uint64_t *dwords = nullptr;
 };

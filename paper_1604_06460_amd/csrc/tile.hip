@@ -1,0 +1,431 @@
+// A run of gates in one pass over the state. A workgroup holds a tile of
+// 2^T amplitudes (the values of T chosen qubits, the lowest ones always
+// among them so that every access moves whole 128-byte lines) in registers,
+// 16 amplitudes per thread, applies every gate of the pass to it and writes
+// it back: the state is read and written once for all of them, where a sweep
+// per fused block moves it for each block of up to six qubits.
+//
+// A pass is a sequence of stages (passes.cpp). In a stage four of the tile's
+// qubits index a thread's 16 registers, so a gate on one or two of them is
+// arithmetic between registers with its matrix in scalar operands. Between
+// stages the tile goes through LDS, which makes four other qubits the
+// register qubits. Diagonal gates and the controls of other gates need no
+// register qubit, nor even a qubit of the tile: they depend on index bits
+// alone, which a thread knows.
+//
+// Complex64 states are computed in FP64 between the exchanges. The
+// compiler's packed FP32 is off, so FP32 and FP64 multiply-adds issue at the
+// same rate here, and a value is rounded once per stage, not once per gate.
+//
+// What bounds it: on large states the FP64 multiply-adds (eight per
+// amplitude and one-qubit gate) and the memory take about the same time;
+// workgroups on a compute unit hide one behind the other.
+#include "qs_internal.h"
+#include "tile.h"
+
+namespace qs {
+namespace {
+
+template <typename S> struct V2;
+template <> struct V2<double> {
+    using T = double2;
+    typedef double N __attribute__((ext_vector_type(2)));
+};
+template <> struct V2<float> {
+    using T = float2;
+    typedef float N __attribute__((ext_vector_type(2)));
+};
+
+typedef const uint64_t __attribute__((address_space(4))) *Words;   // uniform loads
+
+struct TileGeom {
+    int pos[kTileBitsMax];   // absolute tile bit positions, ascending
+    int n_stages;
+};
+
+__device__ __forceinline__ double as_double(uint64_t w) { return __longlong_as_double((long long)w); }
+
+// LDS slot of tile element e. Linear over XOR, so the slot of a thread's
+// register j is the thread's slot XOR a uniform constant; bits p, p + 5 and
+// p + 10 of e choose the same pair of banks, and the planner gives the low
+// lane bits tile bits that differ modulo 5.
+__device__ __forceinline__ uint32_t slot(uint32_t e) { return e ^ ((e >> 5) & 31) ^ ((e >> 10) & 31); }
+
+// Layout of a stage: where the thread's bits and the register bits sit in
+// the tile (LDS slots) and in the state (index bits).
+template <int T>
+struct Layout {
+    uint64_t idx;       // the thread's index bits in the state (register bits zero)
+    uint32_t sl;        // LDS byte offset of register 0
+    uint32_t rs[4];     // XOR of that by register bit b
+    uint64_t ro[4];     // index bit of register bit b
+    __device__ __forceinline__ void set(uint64_t base, uint64_t w0, uint64_t w1, uint64_t w2, uint32_t tid)
+    {
+        uint32_t e = 0;
+        uint64_t a = base;
+#pragma unroll
+        for (int i = 0; i < T - 4; ++i) {
+            const uint32_t b = (tid >> i) & 1;
+            e |= b << ((w0 >> (4 * i)) & 15);
+            a |= uint64_t(b) << ((w1 >> (6 * i)) & 63);
+        }
+        idx = a;
+        sl = 8 * slot(e);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            rs[b] = 8 * slot(1u << ((w0 >> (4 * (T - 4 + b))) & 15));
+            ro[b] = 1ull << ((w2 >> (6 * b)) & 63);
+        }
+    }
+    __device__ __forceinline__ uint32_t at(uint32_t first, int j) const
+    {
+        return first ^ ((j & 1 ? rs[0] : 0) ^ (j & 2 ? rs[1] : 0) ^ (j & 4 ? rs[2] : 0) ^ (j & 8 ? rs[3] : 0));
+    }
+    __device__ __forceinline__ uint64_t off(int j) const
+    {
+        return (j & 1 ? ro[0] : 0) + (j & 2 ? ro[1] : 0) + (j & 4 ? ro[2] : 0) + (j & 8 ? ro[3] : 0);
+    }
+};
+
+// One-qubit gate on the pair of amplitudes p, q, in place: the last
+// multiply-add of each sum overwrites an input that nothing reads any more.
+// Written out, because every path through the operation loop has to leave
+// the tile in the same registers; from plain expressions the compiler makes
+// new values on each path, merges them by copies and spills.
+__device__ __forceinline__ void pair(double &pr, double &pi, double &qr, double &qi, const double (&m)[8])
+{
+    double ur, ui, vr, vi;
+    asm("v_mul_f64 %4, %8, %0\n\t"
+        "v_mul_f64 %5, %8, %1\n\t"
+        "v_mul_f64 %6, %12, %0\n\t"
+        "v_mul_f64 %7, %12, %1\n\t"
+        "v_fma_f64 %4, -%9, %1, %4\n\t"
+        "v_fma_f64 %5, %9, %0, %5\n\t"
+        "v_fma_f64 %6, -%13, %1, %6\n\t"
+        "v_fma_f64 %7, %13, %0, %7\n\t"
+        "v_fma_f64 %4, %10, %2, %4\n\t"
+        "v_fma_f64 %5, %10, %3, %5\n\t"
+        "v_fma_f64 %6, %14, %2, %6\n\t"
+        "v_fma_f64 %7, %15, %2, %7\n\t"
+        "v_fma_f64 %0, -%11, %3, %4\n\t"
+        "v_fma_f64 %1, %11, %2, %5\n\t"
+        "v_fma_f64 %2, -%15, %3, %6\n\t"
+        "v_fma_f64 %3, %14, %3, %7"
+        : "+v"(pr), "+v"(pi), "+v"(qr), "+v"(qi), "=&v"(ur), "=&v"(ui), "=&v"(vr), "=&v"(vi)
+        : "s"(m[0]), "s"(m[1]), "s"(m[2]), "s"(m[3]), "s"(m[4]), "s"(m[5]), "s"(m[6]), "s"(m[7]));
+}
+
+// Amplitude x times the thread's phase f, in place.
+__device__ __forceinline__ void phase(double &xr, double &xi, double fr, double fi)
+{
+    double u, v;
+    asm("v_mul_f64 %2, %5, %1\n\t"
+        "v_mul_f64 %3, %5, %0\n\t"
+        "v_fma_f64 %0, %4, %0, -%2\n\t"
+        "v_fma_f64 %1, %4, %1, %3"
+        : "+v"(xr), "+v"(xi), "=&v"(u), "=&v"(v)
+        : "v"(fr), "v"(fi));
+}
+
+// Flips the sign of x where the top bit of f is set.
+__device__ __forceinline__ void flip(double &x, uint32_t f)
+{
+    uint32_t hi = uint32_t(__double2hiint(x));
+    asm("v_xor_b32 %0, %0, %1" : "+v"(hi) : "v"(f));
+    x = __hiloint2double(int(hi), __double2loint(x));
+}
+
+__device__ __forceinline__ void matrix2(double (&m)[8], Words w)
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i) m[i] = as_double(w[i]);
+}
+
+template <int B>
+__device__ __forceinline__ void dense1(double (&xr)[16], double (&xi)[16], Words w)
+{
+    double m[8];
+    matrix2(m, w);
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+        if (!((j >> B) & 1)) pair(xr[j], xi[j], xr[j | (1 << B)], xi[j | (1 << B)], m);
+}
+
+// The same where controls match: `on` says whether the thread's index bits
+// do, bit j of `amps` whether register j's do.
+template <int B>
+__device__ __forceinline__ void cdense1(double (&xr)[16], double (&xi)[16], Words w, bool on, uint32_t amps)
+{
+    double m[8];
+    matrix2(m, w);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        if ((j >> B) & 1) continue;
+        const int k = j | (1 << B);
+        if (((amps >> j) & 1) && on) pair(xr[j], xi[j], xr[k], xi[k], m);
+    }
+}
+
+// (Controlled) X on register bit B: moves, no arithmetic.
+template <int B>
+__device__ __forceinline__ void xswap(double (&xr)[16], double (&xi)[16], bool on, uint32_t amps)
+{
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        if ((j >> B) & 1) continue;
+        const int k = j | (1 << B);
+        if ((amps >> j) & 1) {
+            const double pr = xr[j], pi = xi[j], qr = xr[k], qi = xi[k];
+            xr[j] = on ? qr : pr;
+            xi[j] = on ? qi : pi;
+            xr[k] = on ? pr : qr;
+            xi[k] = on ? pi : qi;
+        }
+    }
+}
+
+// Two-qubit gate on register bits B0 < B1 (local index bit 0 = B0).
+template <int B0, int B1>
+__device__ __forceinline__ void dense2(double (&xr)[16], double (&xi)[16], Words m)
+{
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        if (((j >> B0) & 1) || ((j >> B1) & 1)) continue;
+        const int at[4] = {j, j | (1 << B0), j | (1 << B1), j | (1 << B0) | (1 << B1)};
+        double vr[4], vi[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            double sr = 0.0, si = 0.0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const double mr = as_double(m[2 * (4 * r + c)]), mi = as_double(m[2 * (4 * r + c) + 1]);
+                sr = fma(-mi, xi[at[c]], fma(mr, xr[at[c]], sr));
+                si = fma(mi, xr[at[c]], fma(mr, xi[at[c]], si));
+            }
+            vr[r] = sr;
+            vi[r] = si;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            xr[at[r]] = vr[r];
+            xi[at[r]] = vi[r];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+template <int B0, int B1>
+__device__ __forceinline__ void swap2(double (&xr)[16], double (&xi)[16])
+{
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        if (!((j >> B0) & 1) || ((j >> B1) & 1)) continue;
+        const int k = (j & ~(1 << B0)) | (1 << B1);
+        const double r = xr[j], i = xi[j];
+        xr[j] = xr[k];
+        xi[j] = xi[k];
+        xr[k] = r;
+        xi[k] = i;
+    }
+}
+
+// Calls f<B0, B1> for the pair number q in (0,1) (0,2) (0,3) (1,2) (1,3) (2,3).
+#define QS_PAIR_CASES(f, q, ...)                     \
+    switch (q) {                                     \
+    case 0: f<0, 1>(__VA_ARGS__); break;             \
+    case 1: f<0, 2>(__VA_ARGS__); break;             \
+    case 2: f<0, 3>(__VA_ARGS__); break;             \
+    case 3: f<1, 2>(__VA_ARGS__); break;             \
+    case 4: f<1, 3>(__VA_ARGS__); break;             \
+    default: f<2, 3>(__VA_ARGS__); break;            \
+    }
+#define QS_BIT_CASES(f, b, ...)                      \
+    switch (b) {                                     \
+    case 0: f<0>(__VA_ARGS__); break;                \
+    case 1: f<1>(__VA_ARGS__); break;                \
+    case 2: f<2>(__VA_ARGS__); break;                \
+    default: f<3>(__VA_ARGS__); break;               \
+    }
+
+// Diagonal gates. Signs first: every term flips the amplitudes of its
+// register mask where the thread's index bits match, gathered in one 16-bit
+// mask per thread. Then groups of phases that change the same registers:
+// their product is formed once per thread, then multiplied in.
+__device__ __forceinline__ Words diagonal(double (&xr)[16], double (&xi)[16], uint64_t h, Words pc, uint64_t idx)
+{
+    const int nsign = int((h >> 8) & 0xffff), ngroup = int((h >> 24) & 0xffff);
+    if (nsign) {
+        const uint32_t any = uint32_t(h >> 40) & 0xffff;
+        uint32_t s = 0;
+        for (int i = 0; i < nsign; ++i) {
+            const bool on = (idx & pc[0]) == pc[1];
+            s ^= on ? uint32_t(pc[2]) : 0u;
+            pc += 3;
+        }
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            if ((any >> j) & 1) {
+                const uint32_t f = (s << (31 - j)) & 0x80000000u;
+                flip(xr[j], f);
+                flip(xi[j], f);
+            }
+        }
+    }
+    for (int g = 0; g < ngroup; ++g) {
+        const uint32_t amps = uint32_t(pc[0]) & 0xffff;
+        const int nt = int(pc[0] >> 16);
+        ++pc;
+        double fr = 1.0, fi = 0.0;
+        for (int i = 0; i < nt; ++i) {
+            const bool on = (idx & pc[0]) == pc[1];
+            const double pr = as_double(pc[2]), pi = as_double(pc[3]);
+            const double r = fma(-pi, fi, pr * fr), q = fma(pi, fr, pr * fi);
+            fr = on ? r : fr;
+            fi = on ? q : fi;
+            pc += 4;
+        }
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            if ((amps >> j) & 1) {
+                phase(xr[j], xi[j], fr, fi);
+            }
+        }
+    }
+    return pc;
+}
+
+template <typename S, int T, bool NT>
+__global__ __launch_bounds__(1 << (T - 4), 3) void k_tile_pass(typename V2<S>::T *__restrict__ psi,
+                                                              const uint64_t *__restrict__ words, TileGeom tg)
+{
+    using N2 = typename V2<S>::N;
+    __shared__ __align__(16) char lds[8 << T];
+    const uint32_t tid = threadIdx.x;
+    uint64_t base = xcd_order<uint64_t, 64>(blockIdx.x, gridDim.x);
+#pragma unroll
+    for (int i = 0; i < T; ++i) {
+        const int p = tg.pos[i];
+        base = ((base >> p) << (p + 1)) | (base & ((1ull << p) - 1));
+    }
+    Words pc = (Words)words;
+    Layout<T> L;
+    L.set(base, pc[0], pc[1], pc[2], tid);
+    double xr[16], xi[16];
+    {
+        const N2 *p = reinterpret_cast<const N2 *>(psi) + L.idx;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            N2 v;
+            if constexpr (NT) v = __builtin_nontemporal_load(p + L.off(j));
+            else v = p[L.off(j)];
+            xr[j] = double(v.x);
+            xi[j] = double(v.y);
+        }
+    }
+    for (int st = 0;; ++st) {
+        int nops = int(pc[2] >> 32);
+        pc += 3;
+        for (; nops > 0; --nops) {
+            const uint64_t h = pc[0];
+            ++pc;
+            const int type = int(h & 0xff);
+            if (type == kTileDiag) {
+                pc = diagonal(xr, xi, h, pc, L.idx);
+            } else if (type == kTileDense1) {
+                QS_BIT_CASES(dense1, int((h >> 8) & 3), xr, xi, pc)
+                pc += 8;
+            } else if (type == kTileCDense1) {
+                const bool on = (L.idx & pc[0]) == pc[1];
+                const uint32_t amps = uint32_t(h >> 16) & 0xffff;
+                QS_BIT_CASES(cdense1, int((h >> 8) & 3), xr, xi, pc + 2, on, amps)
+                pc += 10;
+            } else if (type == kTileX) {
+                const bool on = (L.idx & pc[0]) == pc[1];
+                const uint32_t amps = uint32_t(h >> 16) & 0xffff;
+                QS_BIT_CASES(xswap, int((h >> 8) & 3), xr, xi, on, amps)
+                pc += 2;
+            } else if (type == kTileDense2) {
+                QS_PAIR_CASES(dense2, int((h >> 8) & 7), xr, xi, pc)
+                pc += 32;
+            } else {
+                QS_PAIR_CASES(swap2, int((h >> 8) & 7), xr, xi)
+            }
+        }
+        if (st + 1 >= tg.n_stages) break;
+        Layout<T> M;
+        M.set(base, pc[0], pc[1], pc[2], tid);
+        // the thread's offsets are opaque per half-exchange: the compiler
+        // would keep all 32 of them in registers and spill the tile
+        auto write = [&](auto &&put) {
+            uint32_t first = L.sl;
+            asm volatile("" : "+v"(first));
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < 16; ++j) put(lds + L.at(first, j), j);
+        };
+        auto read = [&](auto &&get) {
+            uint32_t first = M.sl;
+            asm volatile("" : "+v"(first));
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < 16; ++j) get(lds + M.at(first, j), j);
+        };
+        if constexpr (sizeof(S) == 8) {
+            // real parts, then imaginary parts: half the LDS, so that two
+            // workgroups (T = 13) share a compute unit
+            write([&](char *p, int j) { *reinterpret_cast<double *>(p) = xr[j]; });
+            read([&](char *p, int j) { xr[j] = *reinterpret_cast<double *>(p); });
+            write([&](char *p, int j) { *reinterpret_cast<double *>(p) = xi[j]; });
+            read([&](char *p, int j) { xi[j] = *reinterpret_cast<double *>(p); });
+        } else {
+            write([&](char *p, int j) { *reinterpret_cast<float2 *>(p) = float2{float(xr[j]), float(xi[j])}; });
+            read([&](char *p, int j) {
+                const float2 v = *reinterpret_cast<float2 *>(p);
+                xr[j] = double(v.x);
+                xi[j] = double(v.y);
+            });
+        }
+        L = M;
+    }
+    N2 *p = reinterpret_cast<N2 *>(psi) + L.idx;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const N2 v = {S(xr[j]), S(xi[j])};
+        if constexpr (NT) __builtin_nontemporal_store(v, p + L.off(j));
+        else p[L.off(j)] = v;
+    }
+}
+
+template <typename S, int T>
+void launch(qs_state *h, const uint64_t *words, const TileGeom &tg, bool nt)
+{
+    auto *psi = static_cast<typename V2<S>::T *>(h->psi);
+    const dim3 grid(unsigned(h->dim() >> T)), block(1u << (T - 4));
+    if (nt) hipLaunchKernelGGL((k_tile_pass<S, T, true>), grid, block, 0, h->stream, psi, words, tg);
+    else hipLaunchKernelGGL((k_tile_pass<S, T, false>), grid, block, 0, h->stream, psi, words, tg);
+}
+
+}  // namespace
+
+int launch_tile_pass(qs_state *h, const TilePass &p, const uint64_t *dwords)
+{
+    if (p.T > h->n || (h->dim() >> p.T) > 0x7fffffffull)
+        return fail(QS_EUNSUPPORTED, "tile of %d qubits on a %d-qubit state", p.T, h->n);
+    TileGeom tg;
+    for (int i = 0; i < kTileBitsMax; ++i) tg.pos[i] = i < p.T ? p.pos[i] : 0;
+    tg.n_stages = p.n_stages;
+    const uint64_t *w = dwords + p.word0;
+    const bool nt = h->dim() * h->amp_bytes() > (size_t(256) << 20);   // past the last-level cache
+    const bool d = h->dtype == QS_C128;
+    switch (p.T) {
+    case 10: d ? launch<double, 10>(h, w, tg, nt) : launch<float, 10>(h, w, tg, nt); break;
+    case 11: d ? launch<double, 11>(h, w, tg, nt) : launch<float, 11>(h, w, tg, nt); break;
+    case 12: d ? launch<double, 12>(h, w, tg, nt) : launch<float, 12>(h, w, tg, nt); break;
+    case 13: d ? launch<double, 13>(h, w, tg, nt) : launch<float, 13>(h, w, tg, nt); break;
+    default: return fail(QS_EUNSUPPORTED, "tile of %d qubits", p.T);
+    }
+    QS_HIP(hipGetLastError());
+    return QS_OK;
+}
+
+}  // namespace qs

@@ -1,0 +1,144 @@
+"""Passes over register tiles (csrc/tile.hip, passes.cpp) against the oracle:
+every operation of a pass, tiles as large as the state and smaller, gates that
+no pass takes between passes, and programs that a run splits."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# one rounding of each amplitude per stage in complex64 and one per operation
+# in complex128; some hundred of either stay far inside these
+TOL = {1: 1e-10, 0: 1e-5}
+
+
+@pytest.fixture(scope="module")
+def Q():
+    from paper_1604_06460_amd import qs
+    return qs
+
+
+@pytest.fixture(scope="module")
+def O():
+    from oracle import oracle
+    return oracle
+
+
+@pytest.fixture(scope="module")
+def S():
+    from synth import circuits
+    return circuits
+
+
+def _unitary(rng, k):
+    d = 1 << k
+    q, r = np.linalg.qr(rng.standard_normal((d, d)) + 1j * rng.standard_normal((d, d)))
+    return q * (np.diagonal(r) / np.abs(np.diagonal(r)))
+
+
+def _phases(rng, k):
+    """A diagonal gate: ones, minus ones and other phases."""
+    return np.diag([(1.0, -1.0, np.exp(2j * np.pi * rng.random()))[rng.integers(0, 3)] for _ in range(1 << k)])
+
+
+def _circuit(S, rng, n, count, wide):
+    """Gates of every kind a pass knows, and with `wide` some it does not."""
+    gates = []
+    for _ in range(count):
+        q = [int(x) for x in rng.permutation(n)[:5]]
+        cm = 1 << q[3]
+        kind = int(rng.integers(0, 11 if wide else 9))
+        if kind <= 1:
+            gates.append(S.Gate((q[0],), _unitary(rng, 1)))
+        elif kind == 2:
+            gates.append(S.Gate((q[0],), _unitary(rng, 1), cm, cm * int(rng.integers(0, 2))))
+        elif kind == 3:
+            gates.append(S.mcx((q[1], q[2]), q[0]))
+        elif kind == 4:
+            gates.append(S.Gate((q[0],), S.MAT_X))
+        elif kind == 5:
+            k = int(rng.integers(1, 4))
+            gates.append(S.Gate(tuple(q[:k]), _phases(rng, k), cm, cm * int(rng.integers(0, 2))))
+        elif kind == 6:
+            gates.append(S.Gate((q[0], q[1]), _unitary(rng, 2)))
+        elif kind == 7:
+            gates.append(S.swap(q[0], q[1]))
+        elif kind == 8:
+            gates.append(S.Gate((q[0], q[1]), np.array([[1, 0, 0, 0], [0, 1, 0, 0], [0, 0, 0, 1], [0, 0, 1, 0]],
+                                                       dtype=np.complex128)))
+        elif kind == 9:
+            gates.append(S.Gate(tuple(q[:3]), _unitary(rng, 3)))
+        else:
+            gates.append(S.Gate((q[0], q[1]), _unitary(rng, 2), cm, cm))
+    return gates
+
+
+@pytest.mark.parametrize("dtype", [1, 0])
+@pytest.mark.parametrize("n", [10, 11, 12, 13, 15])
+@pytest.mark.parametrize("wide", [False, True])
+def test_every_operation_vs_oracle(Q, O, S, dtype, n, wide):
+    rng = np.random.default_rng(100 * n + 10 * dtype + wide)
+    gates = _circuit(S, rng, n, 90, wide)
+    psi0 = S.normal_state(n, n)
+    if dtype == 0:
+        psi0 = psi0.astype(np.complex64)
+    ref = O.apply_circuit(psi0.astype(np.complex128), gates)
+    for k in (2, 5):
+        st = Q.State(n, dtype)
+        st.set(psi0)
+        st.apply_circuit(gates, k)
+        assert np.abs(st.get() - ref).max() < TOL[dtype]
+        prog = st.compile(gates, k)
+        nb = prog.info()[0]
+        st.set(psi0)
+        st.run(prog)
+        whole = st.get()
+        assert np.abs(whole - ref).max() < TOL[dtype]
+        st.set(psi0)
+        st.run_range(prog, 0, nb // 2)     # in parts: by blocks
+        st.run_range(prog, nb // 2, nb)
+        assert np.abs(st.get() - ref).max() < TOL[dtype]
+        st.free()
+
+
+@pytest.mark.parametrize("dtype", [1, 0])
+def test_large_state_and_lent_buffer(Q, O, S, dtype):
+    """17 qubits: 32 tiles, qubits of a pass far apart, on a torch tensor."""
+    import torch
+    n = 17
+    gates = S.random_layer_circuit(n, 5, 77) + S.qft_circuit(n)
+    psi0 = S.normal_state(n, 3).astype(np.complex128 if dtype else np.complex64)
+    ref = O.apply_circuit(psi0.astype(np.complex128), gates)
+    t = torch.from_numpy(psi0).cuda()
+    st = Q.State(n, dtype, device_buf=t.data_ptr())
+    st.apply_circuit(gates, 4)
+    st.sync()
+    assert np.abs(t.cpu().numpy() - ref).max() < TOL[dtype]
+
+
+def test_moves_are_exact(Q, O, S):
+    """X under any controls and SWAP move amplitudes bit for bit."""
+    n = 13
+    rng = np.random.default_rng(5)
+    gates = []
+    for _ in range(80):
+        q = [int(x) for x in rng.permutation(n)[:4]]
+        gates.append([S.mcx((q[1],), q[0]), S.mcx((q[1], q[2]), q[0]), S.Gate((q[0],), S.MAT_X), S.swap(q[0], q[1])]
+                     [int(rng.integers(0, 4))])
+    psi0 = S.normal_state(n, 9)
+    ref = O.apply_circuit(psi0, gates)
+    st = Q.State(n, 1)
+    st.set(psi0)
+    st.apply_circuit(gates, 4)
+    assert np.array_equal(st.get().view(np.uint64), ref.view(np.uint64))
+
+
+def test_diagonal_circuit(Q, O, S):
+    """Only phases: one pass without a matrix, every term applied at its end."""
+    n = 12
+    rng = np.random.default_rng(6)
+    gates = [S.Gate((int(q[0]), int(q[1])), _phases(rng, 2)) for q in (rng.permutation(n) for _ in range(40))]
+    psi0 = S.normal_state(n, 4)
+    st = Q.State(n, 1)
+    st.set(psi0)
+    st.apply_circuit(gates, 2)
+    assert np.abs(st.get() - O.apply_circuit(psi0, gates)).max() < 1e-10
