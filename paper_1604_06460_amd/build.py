@@ -25,6 +25,10 @@ DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=" + ARCH, "-I", INC, "-I", CSRC,
           "-Wall", "-Wno-unused-result", "-munsafe-fp-atomics"]
 
+# The tile passes keep the whole tile in registers across a loop with uniform
+# branches; structurised, every path around a branch would copy it.
+FILE_FLAGS = {"tile.hip": ["-mllvm", "-structurizecfg-skip-uniform-regions=1"]}
+
 
 def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "*.cpp")))
@@ -32,7 +36,7 @@ def sources():
 
 def _compile(src, verbose):
     obj = os.path.join(BUILD, os.path.basename(src) + ".o")
-    cmd = [HIPCC, "-x", "hip", "-c", src, "-o", obj] + COMMON + DEVICE_FLAGS
+    cmd = [HIPCC, "-x", "hip", "-c", src, "-o", obj] + COMMON + DEVICE_FLAGS + FILE_FLAGS.get(os.path.basename(src), [])
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)

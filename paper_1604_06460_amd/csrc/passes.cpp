@@ -15,6 +15,8 @@
 #include "tile.h"
 
 #include <algorithm>
+#include <cmath>
+#include <complex>
 #include <cstring>
 
 #include "qs_internal.h"
@@ -22,7 +24,9 @@
 namespace qs {
 namespace {
 
-enum Kind { kOne, kTwo, kSwap, kDiagonal, kAlone, kNothing };
+enum Kind { kOne, kRotation, kTwo, kSwap, kDiagonal, kAlone, kNothing };
+
+typedef std::complex<long double> Phase;
 
 struct TGate {
     int kind = kAlone;
@@ -30,8 +34,10 @@ struct TGate {
     uint64_t need = 0;         // qubits the gate is not diagonal on
     uint64_t diag = 0;         // qubits it is diagonal on
     uint64_t cvals = 0;        // kOne: control values (mask: diag)
-    int target[2] = {0, 0};    // kOne, kTwo
+    int target[2] = {0, 0};    // kOne, kRotation, kTwo, kSwap
     double m[8] = {0};         // kOne
+    double r[4] = {0};         // kRotation: diag(a0, a0 after) r diag(1, before)
+    Phase before, after, a0;
     const double *mat = nullptr;
     const int *targets = nullptr;
     int k = 0;
@@ -40,7 +46,7 @@ struct TGate {
 
 struct Term {
     uint64_t mask, vals;
-    double pr, pi;
+    Phase p;
 };
 
 uint64_t word_of(double v)
@@ -78,6 +84,30 @@ bool as_controlled(const double *m, int &ctrl, int &val, double *u)
             return true;
         }
     return false;
+}
+
+// A unitary one-qubit gate as a real matrix (all but a rotation) between
+// phases. False where the matrix is further than rounding from one (it may be
+// any matrix). Every entry keeps its own modulus, so that what rounding left
+// of the gate's norms stays as given: over some hundred gates whose norms are
+// off to the same side it would add up.
+bool as_rotation(TGate &g)
+{
+    Phase u[4], a[4];
+    for (int i = 0; i < 4; ++i) {
+        u[i] = Phase(g.m[2 * i], g.m[2 * i + 1]);
+        g.r[i] = std::hypot(g.m[2 * i], g.m[2 * i + 1]);
+        if (g.r[i] == 0) return false;
+        a[i] = u[i] / (long double)(g.r[i]);
+    }
+    g.r[1] = -g.r[1];
+    g.a0 = a[0];
+    g.after = a[2] / a[0];
+    // the second column's phase, from both of its entries by their weight
+    const Phase b = a[3] / a[2] * (long double)(g.r[3] * g.r[3]) - a[1] / a[0] * (long double)(g.r[1] * g.r[1]);
+    g.before = b / std::abs(b);
+    return std::abs(a[0] * g.before * (long double)(g.r[1]) - u[1]) <= 1e-15L &&
+           std::abs(a[2] * g.before * (long double)(g.r[3]) - u[3]) <= 1e-15L;
 }
 
 void read_gate(int k, const int *targets, const double *m, uint64_t cmask, uint64_t cvals, TGate &g)
@@ -126,6 +156,7 @@ void read_gate(int k, const int *targets, const double *m, uint64_t cmask, uint6
     if (g.kind == kOne) {
         static const double xm[8] = {0, 0, 1, 0, 1, 0, 0, 0};
         g.x = std::equal(g.m, g.m + 8, xm);
+        if (!g.x && !g.diag && as_rotation(g)) g.kind = kRotation;
     }
 }
 
@@ -140,7 +171,7 @@ void add_terms(const TGate &g, std::vector<Term> &out)
         uint64_t v = g.cv;
         for (int i = 0; i < g.k; ++i)
             if ((j >> i) & 1) v |= 1ull << g.targets[i];
-        out.push_back(Term{tm | g.cmask, v, pr, pi});
+        out.push_back(Term{tm | g.cmask, v, Phase(pr, pi)});
     }
 }
 
@@ -161,7 +192,8 @@ struct Planner {
     int n, T, low;                 // low: qubits inside a 128-byte line
     const std::vector<TGate> &gates;
     TilePlan &out;
-    std::vector<Term> pending;
+    std::vector<Term> pending;     // phases not applied yet
+    Phase scale = 1.0L;            // and the one that all amplitudes share
     double flops = 0;              // multiply-adds per amplitude
 
     Planner(int n_, int T_, int low_, const std::vector<TGate> &g, TilePlan &o) : n(n_), T(T_), low(low_), gates(g), out(o) {}
@@ -283,63 +315,85 @@ struct Planner {
         return amps;
     }
 
-    // Applies the waiting terms that involve a qubit of `which` here.
-    int flush(uint64_t which, const int *reg_bit, std::vector<uint64_t> &w)
+    // Applies the waiting terms that involve a qubit of `which` here; all:
+    // every one, and the common phase.
+    int flush(uint64_t which, bool all, const int *reg_bit, std::vector<uint64_t> &w)
     {
         std::vector<Term> keep, now;
-        for (const Term &t : pending) ((t.mask & which) ? now : keep).push_back(t);
-        if (now.empty()) return 0;
+        for (const Term &t : pending) (all || (t.mask & which) ? now : keep).push_back(t);
         pending.swap(keep);
         struct Placed {
             uint32_t amps;
             uint64_t om, ov;
-            double pr, pi;
+            Phase p;
         };
         std::vector<Placed> sign, ph;
+        Phase table[16];
+        std::vector<uint32_t> inside;    // register masks of the terms in the table
+        for (Phase &f : table) f = all ? scale : Phase(1.0L);
+        if (all && scale != Phase(1.0L)) inside.push_back(0xffff);
+        if (all) scale = 1.0L;
         uint32_t any = 0;
         for (const Term &t : now) {
             Placed q;
             q.amps = registers(reg_bit, t.mask, t.vals, q.om, q.ov);
-            q.pr = t.pr;
-            q.pi = t.pi;
-            if (t.pr == -1.0 && t.pi == 0.0) {
+            q.p = t.p;
+            if (!q.om) {
+                for (int j = 0; j < 16; ++j)
+                    if ((q.amps >> j) & 1) table[j] *= t.p;
+                if (std::find(inside.begin(), inside.end(), q.amps) == inside.end()) inside.push_back(q.amps);
+            } else if (t.p == Phase(-1.0L) && sign.size() < 0xffff) {
                 sign.push_back(q);
                 any |= q.amps;
             } else {
                 ph.push_back(q);
             }
         }
-        int ops = 0;
-        size_t s = 0;
         std::stable_sort(ph.begin(), ph.end(), [](const Placed &a, const Placed &b) { return a.amps < b.amps; });
+        // one set of registers: a group without conditions instead of a table
+        const bool one = inside.size() == 1;
+        const uint32_t set = one ? inside[0] : 0;
+        const bool tab = inside.size() > 1;
+        if (!one && !tab && sign.empty() && ph.empty()) return 0;
         const size_t head = w.size();
         w.push_back(0);
-        const uint64_t ns = std::min<size_t>(sign.size(), 0xffff);
-        for (; s < ns; ++s) {
-            w.push_back(sign[s].om);
-            w.push_back(sign[s].ov);
-            w.push_back(sign[s].amps);
+        auto put = [&](const Phase &f) {
+            w.push_back(word_of(double(f.real())));
+            w.push_back(word_of(double(f.imag())));
+        };
+        if (tab) {
+            for (const Phase &f : table) put(f);
+            flops += 4;
         }
-        for (; s < sign.size(); ++s) ph.push_back(sign[s]);   // past the count's range
+        for (const Placed &q : sign) {
+            w.push_back(q.om);
+            w.push_back(q.ov);
+            w.push_back(q.amps);
+        }
         uint64_t groups = 0;
-        for (size_t i = 0; i < ph.size();) {
+        bool placed = !one;
+        for (size_t i = 0; i < ph.size() || !placed;) {
+            const bool lone = !placed && (i >= ph.size() || ph[i].amps > set);
+            const uint32_t amps = lone ? set : ph[i].amps;
             size_t e = i;
-            while (e < ph.size() && ph[e].amps == ph[i].amps) ++e;
-            w.push_back(uint64_t(ph[i].amps) | uint64_t(e - i) << 16);
+            while (!lone && e < ph.size() && ph[e].amps == amps) ++e;
+            w.push_back(uint64_t(amps) | uint64_t(e - i) << 16);
+            const bool first = one && amps == set;
+            put(first ? table[__builtin_ctz(set)] : Phase(1.0L));
+            placed = placed || first;
             for (size_t j = i; j < e; ++j) {
                 w.push_back(ph[j].om);
                 w.push_back(ph[j].ov);
-                w.push_back(word_of(ph[j].pr));
-                w.push_back(word_of(ph[j].pi));
+                put(ph[j].p);
             }
             ++groups;
-            flops += 4.0 * bits(ph[i].amps) / 16.0 + (e - i);
+            flops += 4.0 * bits(amps) / 16.0 + double(e - i);
             i = e;
         }
-        flops += ns ? 2.0 + 0.25 * double(ns) : 0.0;
-        w[head] = uint64_t(kTileDiag) | ns << 8 | groups << 24 | uint64_t(any) << 40;
-        ++ops;
-        return ops;
+        flops += sign.empty() ? 0.0 : 2.0 + 0.25 * double(sign.size());
+        w[head] = uint64_t(kTileDiag) | uint64_t(sign.size()) << 8 | groups << 24 | uint64_t(any) << 40 |
+                  uint64_t(tab) << 56;
+        return 1;
     }
 
     static int reg_of(const int *reg_bit, int q)
@@ -351,6 +405,12 @@ struct Planner {
 
     int emit_gate(const TGate &g, const int *reg_bit, std::vector<uint64_t> &w)
     {
+        if (g.kind == kRotation) {
+            w.push_back(uint64_t(kTileRotate) | uint64_t(reg_of(reg_bit, g.target[0])) << 8);
+            for (int i = 0; i < 4; ++i) w.push_back(word_of(g.r[i]));
+            flops += 4;
+            return 1;
+        }
         if (g.kind == kOne) {
             const uint64_t b = uint64_t(reg_of(reg_bit, g.target[0]));
             if (!g.diag && !g.x) {
@@ -374,9 +434,17 @@ struct Planner {
         static const int pair_no[4][4] = {{0, 0, 1, 2}, {0, 0, 3, 4}, {0, 0, 0, 5}, {0, 0, 0, 0}};
         const uint64_t q = uint64_t(pair_no[lo][hi]);
         if (g.kind == kSwap) {
-            w.push_back(uint64_t(kTileSwap) | q << 8);
-            flops += 2;
-            return 1;
+            // X on one under the other, back, and again
+            for (int i = 0; i < 3; ++i) {
+                const int x = i & 1 ? b : a, ctl = i & 1 ? a : b;
+                uint32_t amps = 0;
+                for (int j = 0; j < 16; ++j) amps |= uint32_t((j >> ctl) & 1) << j;
+                w.push_back(uint64_t(kTileX) | uint64_t(x) << 8 | uint64_t(amps) << 16);
+                w.push_back(0);
+                w.push_back(0);
+            }
+            flops += 6;
+            return 3;
         }
         w.push_back(uint64_t(kTileDense2) | q << 8);
         auto loc = [&](int i) { return a < b ? i : ((i & 1) << 1) | (i >> 1); };   // local bit 0 = lower register
@@ -434,18 +502,45 @@ struct Planner {
             layout(p, s.regs, out.words, reg_bit);
             const size_t head = out.words.size() - 1;
             uint64_t ops = 0;
-            for (int gi : s.gates) {
-                const TGate &g = gates[size_t(gi)];
-                if (g.kind == kDiagonal) {
-                    add_terms(g, pending);
-                    continue;
+            // Rounds: the diagonal gates that come first, the phases in front
+            // of the rotations, then at most one gate per qubit, so that one
+            // diagonal operation serves up to four gates.
+            std::vector<int> todo = s.gates;
+            while (!todo.empty()) {
+                std::vector<int> rest, round;
+                Skipped sk;
+                uint64_t used = 0;
+                for (int gi : todo) {
+                    const TGate &g = gates[size_t(gi)];
+                    // a gate of this round is applied after its phases
+                    const bool take = !sk.blocks(g) && !((g.need | g.diag) & used);
+                    if (!take) {
+                        sk.add(g);
+                        rest.push_back(gi);
+                    } else if (g.kind == kDiagonal) {
+                        add_terms(g, pending);
+                    } else {
+                        if (g.kind == kRotation && g.before != Phase(1.0L))
+                            pending.push_back(Term{g.need, g.need, g.before});
+                        used |= g.need;
+                        round.push_back(gi);
+                    }
                 }
+                uint64_t need = 0;
+                for (int gi : round) need |= gates[size_t(gi)].need;
                 bool clash = false;
-                for (const Term &t : pending) clash = clash || (t.mask & g.need);
-                if (clash) ops += uint64_t(flush(s.regs, reg_bit, out.words));
-                ops += uint64_t(emit_gate(g, reg_bit, out.words));
+                for (const Term &t : pending) clash = clash || (t.mask & need);
+                if (clash) ops += uint64_t(flush(s.regs, false, reg_bit, out.words));
+                for (int gi : round) {
+                    const TGate &g = gates[size_t(gi)];
+                    ops += uint64_t(emit_gate(g, reg_bit, out.words));
+                    if (g.kind != kRotation) continue;
+                    scale *= g.a0;
+                    if (g.after != Phase(1.0L)) pending.push_back(Term{g.need, g.need, g.after});
+                }
+                todo.swap(rest);
             }
-            if (last && si + 1 == st.size()) ops += uint64_t(flush(~0ull, reg_bit, out.words));
+            if (last && si + 1 == st.size()) ops += uint64_t(flush(0, true, reg_bit, out.words));
             out.words[head] |= ops << 32;
         }
         p.n_stages = int(st.size());

@@ -25,10 +25,11 @@ enum TileOp {
     kTileCDense1 = 1,   // | register bit << 8 | register mask << 16; index mask, index values, matrix
     kTileX = 2,         // | register bit << 8 | register mask << 16; index mask, index values
     kTileDense2 = 3,    // | pair << 8; matrix (32 doubles)
-    kTileSwap = 4,      // | pair << 8
-    kTileDiag = 5,      // | signs << 8 | groups << 24 | union of the signs' register masks << 40;
-                        // per sign: index mask, index values, register mask; per group: register mask |
-                        // terms << 16, per term: index mask, index values, phase (2 doubles)
+    kTileRotate = 4,    // | register bit << 8; real matrix (4 doubles)
+    kTileDiag = 5,      // | signs << 8 | groups << 24 | union of the signs' register masks << 40 | table << 56;
+                        // with a table: 16 phases; per sign: index mask, index values, register mask; per
+                        // group: register mask | terms << 16, first phase, per term: index mask, index
+                        // values, phase (a phase: 2 doubles)
 };
 
 struct TilePass {

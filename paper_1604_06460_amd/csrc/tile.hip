@@ -127,11 +127,23 @@ __device__ __forceinline__ void phase(double &xr, double &xi, double fr, double 
         : "v"(fr), "v"(fi));
 }
 
-// Flips the sign of x where the top bit of f is set.
-__device__ __forceinline__ void flip(double &x, uint32_t f)
+// Amplitude x times a phase that all threads share, in place.
+__device__ __forceinline__ void uphase(double &xr, double &xi, double fr, double fi)
+{
+    double u, v;
+    asm("v_mul_f64 %2, %5, %1\n\t"
+        "v_mul_f64 %3, %5, %0\n\t"
+        "v_fma_f64 %0, %4, %0, -%2\n\t"
+        "v_fma_f64 %1, %4, %1, %3"
+        : "+v"(xr), "+v"(xi), "=&v"(u), "=&v"(v)
+        : "s"(fr), "s"(fi));
+}
+
+// Flips the sign of x where the top bit of f is set: hi ^ (f & top).
+__device__ __forceinline__ void flip(double &x, uint32_t f, uint32_t top)
 {
     uint32_t hi = uint32_t(__double2hiint(x));
-    asm("v_xor_b32 %0, %0, %1" : "+v"(hi) : "v"(f));
+    asm("v_bitop3_b32 %0, %0, %1, %2 bitop3:0x78" : "+v"(hi) : "v"(f), "s"(top));
     x = __hiloint2double(int(hi), __double2loint(x));
 }
 
@@ -151,35 +163,98 @@ __device__ __forceinline__ void dense1(double (&xr)[16], double (&xi)[16], Words
         if (!((j >> B) & 1)) pair(xr[j], xi[j], xr[j | (1 << B)], xi[j | (1 << B)], m);
 }
 
-// The same where controls match: `on` says whether the thread's index bits
-// do, bit j of `amps` whether register j's do.
+// Real matrix on register bit B: what is left of a unitary once its phases
+// have joined the diagonal gates around it. Half the multiply-adds of a
+// complex one.
+template <int B>
+__device__ __forceinline__ void rotate1(double (&xr)[16], double (&xi)[16], Words w)
+{
+    const double a = as_double(w[0]), b = as_double(w[1]), c = as_double(w[2]), d = as_double(w[3]);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        if ((j >> B) & 1) continue;
+        const int k = j | (1 << B);
+        double t0, t1, t2, t3;
+        asm("v_mul_f64 %4, %10, %0\n\t"
+            "v_mul_f64 %5, %10, %1\n\t"
+            "v_mul_f64 %6, %9, %2\n\t"
+            "v_mul_f64 %7, %9, %3\n\t"
+            "v_fma_f64 %0, %8, %0, %6\n\t"
+            "v_fma_f64 %1, %8, %1, %7\n\t"
+            "v_fma_f64 %2, %11, %2, %4\n\t"
+            "v_fma_f64 %3, %11, %3, %5"
+            : "+v"(xr[j]), "+v"(xi[j]), "+v"(xr[k]), "+v"(xi[k]), "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3)
+            : "s"(a), "s"(b), "s"(c), "s"(d));
+    }
+}
+
+// The same as dense1 where controls match: `on` says whether the thread's index bits
+// do, bit j of `amps` whether register j's do. A thread whose bits do not
+// match multiplies by the identity, exactly: a branch on `on` would make the
+// compiler copy the tile on every path around it.
+__device__ __forceinline__ void cpair(double &pr, double &pi, double &qr, double &qi, const double (&m)[8])
+{
+    double ur, ui, vr, vi;
+    asm("v_mul_f64 %4, %8, %0\n\t"
+        "v_mul_f64 %5, %8, %1\n\t"
+        "v_mul_f64 %6, %12, %0\n\t"
+        "v_mul_f64 %7, %12, %1\n\t"
+        "v_fma_f64 %4, -%9, %1, %4\n\t"
+        "v_fma_f64 %5, %9, %0, %5\n\t"
+        "v_fma_f64 %6, -%13, %1, %6\n\t"
+        "v_fma_f64 %7, %13, %0, %7\n\t"
+        "v_fma_f64 %4, %10, %2, %4\n\t"
+        "v_fma_f64 %5, %10, %3, %5\n\t"
+        "v_fma_f64 %6, %14, %2, %6\n\t"
+        "v_fma_f64 %7, %15, %2, %7\n\t"
+        "v_fma_f64 %0, -%11, %3, %4\n\t"
+        "v_fma_f64 %1, %11, %2, %5\n\t"
+        "v_fma_f64 %2, -%15, %3, %6\n\t"
+        "v_fma_f64 %3, %14, %3, %7"
+        : "+v"(pr), "+v"(pi), "+v"(qr), "+v"(qi), "=&v"(ur), "=&v"(ui), "=&v"(vr), "=&v"(vi)
+        : "v"(m[0]), "v"(m[1]), "v"(m[2]), "v"(m[3]), "v"(m[4]), "v"(m[5]), "v"(m[6]), "v"(m[7]));
+}
+
 template <int B>
 __device__ __forceinline__ void cdense1(double (&xr)[16], double (&xi)[16], Words w, bool on, uint32_t amps)
 {
     double m[8];
     matrix2(m, w);
 #pragma unroll
+    for (int i = 0; i < 8; ++i) m[i] = on ? m[i] : (i == 0 || i == 6 ? 1.0 : 0.0);
+#pragma unroll
     for (int j = 0; j < 16; ++j) {
         if ((j >> B) & 1) continue;
         const int k = j | (1 << B);
-        if (((amps >> j) & 1) && on) pair(xr[j], xi[j], xr[k], xi[k], m);
+        if ((amps >> j) & 1) cpair(xr[j], xi[j], xr[k], xi[k], m);
     }
+}
+
+// Exchanges two values where the mask is all ones (zero: leaves them).
+__device__ __forceinline__ void exchange(double &a, double &b, uint32_t mask)
+{
+    uint32_t al = uint32_t(__double2loint(a)), ah = uint32_t(__double2hiint(a));
+    uint32_t bl = uint32_t(__double2loint(b)), bh = uint32_t(__double2hiint(b)), t;
+    asm("v_xor_b32 %2, %0, %1\n\tv_and_b32 %2, %2, %3\n\tv_xor_b32 %0, %0, %2\n\tv_xor_b32 %1, %1, %2"
+        : "+v"(al), "+v"(bl), "=&v"(t) : "v"(mask));
+    asm("v_xor_b32 %2, %0, %1\n\tv_and_b32 %2, %2, %3\n\tv_xor_b32 %0, %0, %2\n\tv_xor_b32 %1, %1, %2"
+        : "+v"(ah), "+v"(bh), "=&v"(t) : "v"(mask));
+    a = __hiloint2double(int(ah), int(al));
+    b = __hiloint2double(int(bh), int(bl));
 }
 
 // (Controlled) X on register bit B: moves, no arithmetic.
 template <int B>
 __device__ __forceinline__ void xswap(double (&xr)[16], double (&xi)[16], bool on, uint32_t amps)
 {
+    const uint32_t mask = on ? ~0u : 0u;
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
         if ((j >> B) & 1) continue;
         const int k = j | (1 << B);
         if ((amps >> j) & 1) {
-            const double pr = xr[j], pi = xi[j], qr = xr[k], qi = xi[k];
-            xr[j] = on ? qr : pr;
-            xi[j] = on ? qi : pi;
-            xr[k] = on ? pr : qr;
-            xi[k] = on ? pi : qi;
+            exchange(xr[j], xr[k], mask);
+            exchange(xi[j], xi[k], mask);
         }
     }
 }
@@ -207,25 +282,10 @@ __device__ __forceinline__ void dense2(double (&xr)[16], double (&xi)[16], Words
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            xr[at[r]] = vr[r];
-            xi[at[r]] = vi[r];
+            asm("v_mov_b64 %0, %1" : "+v"(xr[at[r]]) : "v"(vr[r]));
+            asm("v_mov_b64 %0, %1" : "+v"(xi[at[r]]) : "v"(vi[r]));
         }
         __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
-template <int B0, int B1>
-__device__ __forceinline__ void swap2(double (&xr)[16], double (&xi)[16])
-{
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        if (!((j >> B0) & 1) || ((j >> B1) & 1)) continue;
-        const int k = (j & ~(1 << B0)) | (1 << B1);
-        const double r = xr[j], i = xi[j];
-        xr[j] = xr[k];
-        xi[j] = xi[k];
-        xr[k] = r;
-        xi[k] = i;
     }
 }
 
@@ -247,35 +307,39 @@ __device__ __forceinline__ void swap2(double (&xr)[16], double (&xi)[16])
     default: f<3>(__VA_ARGS__); break;               \
     }
 
-// Diagonal gates. Signs first: every term flips the amplitudes of its
-// register mask where the thread's index bits match, gathered in one 16-bit
-// mask per thread. Then groups of phases that change the same registers:
-// their product is formed once per thread, then multiplied in.
+// Diagonal gates. First the phases that depend on register bits alone, as
+// one factor per register, multiplied together by the planner. Then signs:
+// every term flips the amplitudes of its register mask where the thread's
+// index bits match, gathered in one 16-bit mask per thread. Then groups of
+// phases that change the same registers: their product is formed once per
+// thread, then multiplied in.
 __device__ __forceinline__ Words diagonal(double (&xr)[16], double (&xi)[16], uint64_t h, Words pc, uint64_t idx)
 {
+    if (h >> 56) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) uphase(xr[j], xi[j], as_double(pc[2 * j]), as_double(pc[2 * j + 1]));
+        pc += 32;
+    }
     const int nsign = int((h >> 8) & 0xffff), ngroup = int((h >> 24) & 0xffff);
     if (nsign) {
-        const uint32_t any = uint32_t(h >> 40) & 0xffff;
         uint32_t s = 0;
         for (int i = 0; i < nsign; ++i) {
-            const bool on = (idx & pc[0]) == pc[1];
-            s ^= on ? uint32_t(pc[2]) : 0u;
+            const uint32_t amps = uint32_t(pc[2]);   // read first: a load under a condition is a branch
+            s ^= (idx & pc[0]) == pc[1] ? amps : 0u;
             pc += 3;
         }
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            if ((any >> j) & 1) {
-                const uint32_t f = (s << (31 - j)) & 0x80000000u;
-                flip(xr[j], f);
-                flip(xi[j], f);
-            }
+        for (int j = 0; j < 16; ++j) {   // all 16: a branch around each costs more
+            const uint32_t f = s << (31 - j);
+            flip(xr[j], f, 0x80000000u);
+            flip(xi[j], f, 0x80000000u);
         }
     }
     for (int g = 0; g < ngroup; ++g) {
         const uint32_t amps = uint32_t(pc[0]) & 0xffff;
         const int nt = int(pc[0] >> 16);
-        ++pc;
-        double fr = 1.0, fi = 0.0;
+        double fr = as_double(pc[1]), fi = as_double(pc[2]);
+        pc += 3;
         for (int i = 0; i < nt; ++i) {
             const bool on = (idx & pc[0]) == pc[1];
             const double pr = as_double(pc[2]), pi = as_double(pc[3]);
@@ -295,7 +359,7 @@ __device__ __forceinline__ Words diagonal(double (&xr)[16], double (&xi)[16], ui
 }
 
 template <typename S, int T, bool NT>
-__global__ __launch_bounds__(1 << (T - 4), 3) void k_tile_pass(typename V2<S>::T *__restrict__ psi,
+__global__ __launch_bounds__(1 << (T - 4), 4) void k_tile_pass(typename V2<S>::T *__restrict__ psi,
                                                               const uint64_t *__restrict__ words, TileGeom tg)
 {
     using N2 = typename V2<S>::N;
@@ -331,6 +395,9 @@ __global__ __launch_bounds__(1 << (T - 4), 3) void k_tile_pass(typename V2<S>::T
             const int type = int(h & 0xff);
             if (type == kTileDiag) {
                 pc = diagonal(xr, xi, h, pc, L.idx);
+            } else if (type == kTileRotate) {
+                QS_BIT_CASES(rotate1, int((h >> 8) & 3), xr, xi, pc)
+                pc += 4;
             } else if (type == kTileDense1) {
                 QS_BIT_CASES(dense1, int((h >> 8) & 3), xr, xi, pc)
                 pc += 8;
@@ -344,11 +411,9 @@ __global__ __launch_bounds__(1 << (T - 4), 3) void k_tile_pass(typename V2<S>::T
                 const uint32_t amps = uint32_t(h >> 16) & 0xffff;
                 QS_BIT_CASES(xswap, int((h >> 8) & 3), xr, xi, on, amps)
                 pc += 2;
-            } else if (type == kTileDense2) {
+            } else {
                 QS_PAIR_CASES(dense2, int((h >> 8) & 7), xr, xi, pc)
                 pc += 32;
-            } else {
-                QS_PAIR_CASES(swap2, int((h >> 8) & 7), xr, xi)
             }
         }
         if (st + 1 >= tg.n_stages) break;
