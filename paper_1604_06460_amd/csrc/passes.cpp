@@ -18,6 +18,7 @@
 #include <cmath>
 #include <complex>
 #include <cstring>
+#include <initializer_list>
 
 #include "qs_internal.h"
 
@@ -333,7 +334,6 @@ struct Planner {
         for (Phase &f : table) f = all ? scale : Phase(1.0L);
         if (all && scale != Phase(1.0L)) inside.push_back(0xffff);
         if (all) scale = 1.0L;
-        uint32_t any = 0;
         for (const Term &t : now) {
             Placed q;
             q.amps = registers(reg_bit, t.mask, t.vals, q.om, q.ov);
@@ -342,9 +342,8 @@ struct Planner {
                 for (int j = 0; j < 16; ++j)
                     if ((q.amps >> j) & 1) table[j] *= t.p;
                 if (std::find(inside.begin(), inside.end(), q.amps) == inside.end()) inside.push_back(q.amps);
-            } else if (t.p == Phase(-1.0L) && sign.size() < 0xffff) {
+            } else if (t.p == Phase(-1.0L) && sign.size() < 0xfff * kTileSigns) {
                 sign.push_back(q);
-                any |= q.amps;
             } else {
                 ph.push_back(q);
             }
@@ -365,6 +364,8 @@ struct Planner {
             for (const Phase &f : table) put(f);
             flops += 4;
         }
+        flops += sign.empty() ? 0.0 : 2.0 + 0.25 * double(sign.size());
+        while (sign.size() % kTileSigns) sign.push_back(Placed{0, 0, 0, Phase()});   // flips nothing
         for (const Placed &q : sign) {
             w.push_back(q.om);
             w.push_back(q.ov);
@@ -390,9 +391,8 @@ struct Planner {
             flops += 4.0 * bits(amps) / 16.0 + double(e - i);
             i = e;
         }
-        flops += sign.empty() ? 0.0 : 2.0 + 0.25 * double(sign.size());
-        w[head] = uint64_t(kTileDiag) | uint64_t(sign.size()) << 8 | groups << 24 | uint64_t(any) << 40 |
-                  uint64_t(tab) << 56;
+        w[head] = uint64_t(kTileDiag) | uint64_t(tab) << 6 | uint64_t(sign.size() / kTileSigns) << 8 | groups << 20 |
+                  uint64_t(w.size() - head) << 32;
         return 1;
     }
 
@@ -403,57 +403,51 @@ struct Planner {
         return -1;
     }
 
+    void emit(std::vector<uint64_t> &w, int kind, int arg, uint32_t amps, std::initializer_list<uint64_t> masks,
+              const double *m, int count) const
+    {
+        w.push_back(uint64_t(kind) | uint64_t(arg) << 3 | uint64_t(amps) << 8 |
+                    uint64_t(1 + masks.size() + size_t(count)) << 32);
+        w.insert(w.end(), masks);
+        for (int i = 0; i < count; ++i) w.push_back(word_of(m[i]));
+    }
+
     int emit_gate(const TGate &g, const int *reg_bit, std::vector<uint64_t> &w)
     {
+        const int a = reg_of(reg_bit, g.target[0]);
         if (g.kind == kRotation) {
-            w.push_back(uint64_t(kTileRotate) | uint64_t(reg_of(reg_bit, g.target[0])) << 8);
-            for (int i = 0; i < 4; ++i) w.push_back(word_of(g.r[i]));
+            emit(w, kTileRotate, a, 0, {}, g.r, 4);
             flops += 4;
             return 1;
         }
         if (g.kind == kOne) {
-            const uint64_t b = uint64_t(reg_of(reg_bit, g.target[0]));
-            if (!g.diag && !g.x) {
-                w.push_back(uint64_t(kTileDense1) | b << 8);
-                for (int i = 0; i < 8; ++i) w.push_back(word_of(g.m[i]));
-                flops += 8;
-                return 1;
-            }
-            uint64_t om, ov;
-            const uint32_t amps = registers(reg_bit, g.diag, g.cvals, om, ov);
-            w.push_back(uint64_t(g.x ? kTileX : kTileCDense1) | b << 8 | uint64_t(amps) << 16);
-            w.push_back(om);
-            w.push_back(ov);
-            if (!g.x)
-                for (int i = 0; i < 8; ++i) w.push_back(word_of(g.m[i]));
             flops += g.x ? 2 : 8;
+            uint64_t om = 0, ov = 0;
+            const uint32_t amps = registers(reg_bit, g.diag, g.cvals, om, ov);
+            if (g.x) emit(w, kTileX, a, amps, {om, ov}, nullptr, 0);
+            else if (g.diag) emit(w, kTileCDense1, a, amps, {om, ov}, g.m, 8);
+            else emit(w, kTileDense1, a, 0, {}, g.m, 8);
             return 1;
         }
-        const int a = reg_of(reg_bit, g.target[0]), b = reg_of(reg_bit, g.target[1]);
-        const int lo = std::min(a, b), hi = std::max(a, b);
-        static const int pair_no[4][4] = {{0, 0, 1, 2}, {0, 0, 3, 4}, {0, 0, 0, 5}, {0, 0, 0, 0}};
-        const uint64_t q = uint64_t(pair_no[lo][hi]);
+        const int b = reg_of(reg_bit, g.target[1]);
         if (g.kind == kSwap) {
             // X on one under the other, back, and again
             for (int i = 0; i < 3; ++i) {
                 const int x = i & 1 ? b : a, ctl = i & 1 ? a : b;
                 uint32_t amps = 0;
                 for (int j = 0; j < 16; ++j) amps |= uint32_t((j >> ctl) & 1) << j;
-                w.push_back(uint64_t(kTileX) | uint64_t(x) << 8 | uint64_t(amps) << 16);
-                w.push_back(0);
-                w.push_back(0);
+                emit(w, kTileX, x, amps, {0, 0}, nullptr, 0);
             }
             flops += 6;
             return 3;
         }
-        w.push_back(uint64_t(kTileDense2) | q << 8);
-        auto loc = [&](int i) { return a < b ? i : ((i & 1) << 1) | (i >> 1); };   // local bit 0 = lower register
+        // local bit 0 = the lower register bit
+        static const int pair_no[4][4] = {{0, 0, 1, 2}, {0, 0, 3, 4}, {0, 0, 0, 5}, {0, 0, 0, 0}};
+        auto loc = [&](int i) { return a < b ? i : ((i & 1) << 1) | (i >> 1); };
+        double m[32];
         for (int r = 0; r < 4; ++r)
-            for (int c = 0; c < 4; ++c) {
-                const double *e = g.mat + 2 * (4 * loc(r) + loc(c));
-                w.push_back(word_of(e[0]));
-                w.push_back(word_of(e[1]));
-            }
+            for (int c = 0; c < 4; ++c) std::copy_n(g.mat + 2 * (4 * loc(r) + loc(c)), 2, m + 2 * (4 * r + c));
+        emit(w, kTileDense2, pair_no[std::min(a, b)][std::max(a, b)], 0, {}, m, 32);
         flops += 18;
         return 1;
     }
@@ -604,6 +598,7 @@ bool plan_tiles(int n, size_t amp_bytes, const qs_circuit *c, TilePlan &out)
         left.swap(rest);
         pl.pass(S, ex, left.empty() || gates[size_t(left[0])].kind == kAlone);
     }
+    out.words.insert(out.words.end(), size_t(kTileAhead), 0);
     // Estimated time in sweeps: a pass moves the state as a sweep does, with
     // longer strides, and its multiply-adds hide behind the memory in part
     // (30 TFMA/s against 6 TB/s); an unfused gate on up to four qubits is a

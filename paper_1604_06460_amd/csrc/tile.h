@@ -19,18 +19,23 @@ constexpr int kTileBitsMin = 10, kTileBitsMax = 13;   // qubits of a tile
 //           bit b at 4(T - 4 + b)
 //   word 1: state bit of thread bit i at 6i
 //   word 2: state bit of register bit b at 6b, operation count at bit 32
-// An operation's first word holds its kind in the low byte:
+// An operation's first word holds its kind in bits 0-2, a register bit or
+// pair of them in bits 3-5, and its length in words from bit 32. The kernel
+// reads kTileAhead words at the start of every operation, so the stream ends
+// with as many unused ones.
 enum TileOp {
-    kTileDense1 = 0,    // | register bit << 8; matrix (8 doubles)
-    kTileCDense1 = 1,   // | register bit << 8 | register mask << 16; index mask, index values, matrix
-    kTileX = 2,         // | register bit << 8 | register mask << 16; index mask, index values
-    kTileDense2 = 3,    // | pair << 8; matrix (32 doubles)
-    kTileRotate = 4,    // | register bit << 8; real matrix (4 doubles)
-    kTileDiag = 5,      // | signs << 8 | groups << 24 | union of the signs' register masks << 40 | table << 56;
-                        // with a table: 16 phases; per sign: index mask, index values, register mask; per
-                        // group: register mask | terms << 16, first phase, per term: index mask, index
-                        // values, phase (a phase: 2 doubles)
+    kTileDense1 = 0,    // matrix (8 doubles)
+    kTileCDense1 = 1,   // register mask at bit 8; index mask, index values, matrix
+    kTileX = 2,         // register mask at bit 8; index mask, index values
+    kTileDense2 = 3,    // matrix (32 doubles)
+    kTileRotate = 4,    // real matrix (4 doubles)
+    kTileDiag = 5,      // bit 6: a table of 16 phases first; at bit 8 the number of sign blocks (each two
+                        // times index mask, index values, register mask), at bit 20 that of phase groups
+                        // (register mask | terms << 16, first phase; per term: index mask, index values,
+                        // phase). A phase is 2 doubles.
 };
+constexpr int kTileAhead = 8;
+constexpr int kTileSigns = 2;   // signs in a block
 
 struct TilePass {
     int T = 0;

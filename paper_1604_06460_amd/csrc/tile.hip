@@ -37,6 +37,7 @@ template <> struct V2<float> {
 };
 
 typedef const uint64_t __attribute__((address_space(4))) *Words;   // uniform loads
+typedef uint64_t Head __attribute__((ext_vector_type(kTileAhead), aligned(8)));
 
 struct TileGeom {
     int pos[kTileBitsMax];   // absolute tile bit positions, ascending
@@ -167,9 +168,9 @@ __device__ __forceinline__ void dense1(double (&xr)[16], double (&xi)[16], Words
 // have joined the diagonal gates around it. Half the multiply-adds of a
 // complex one.
 template <int B>
-__device__ __forceinline__ void rotate1(double (&xr)[16], double (&xi)[16], Words w)
+__device__ __forceinline__ void rotate1(double (&xr)[16], double (&xi)[16], const Head &w)
 {
-    const double a = as_double(w[0]), b = as_double(w[1]), c = as_double(w[2]), d = as_double(w[3]);
+    const double a = as_double(w[1]), b = as_double(w[2]), c = as_double(w[3]), d = as_double(w[4]);
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
         if ((j >> B) & 1) continue;
@@ -221,7 +222,10 @@ __device__ __forceinline__ void cdense1(double (&xr)[16], double (&xi)[16], Word
     double m[8];
     matrix2(m, w);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) m[i] = on ? m[i] : (i == 0 || i == 6 ? 1.0 : 0.0);
+    for (int i = 0; i < 8; ++i) {
+        asm("" : "+s"(m[i]));   // keeps the load out of the condition: a branch around it
+        m[i] = on ? m[i] : (i == 0 || i == 6 ? 1.0 : 0.0);
+    }
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
         if ((j >> B) & 1) continue;
@@ -313,20 +317,23 @@ __device__ __forceinline__ void dense2(double (&xr)[16], double (&xi)[16], Words
 // index bits match, gathered in one 16-bit mask per thread. Then groups of
 // phases that change the same registers: their product is formed once per
 // thread, then multiplied in.
-__device__ __forceinline__ Words diagonal(double (&xr)[16], double (&xi)[16], uint64_t h, Words pc, uint64_t idx)
+__device__ __forceinline__ void diagonal(double (&xr)[16], double (&xi)[16], uint32_t h, Words pc, uint64_t idx)
 {
-    if (h >> 56) {
+    const int nsign = int(h >> 8) & 0xfff, ngroup = int(h >> 20) & 0xfff;
+    if ((h >> 6) & 1) {
 #pragma unroll
         for (int j = 0; j < 16; ++j) uphase(xr[j], xi[j], as_double(pc[2 * j]), as_double(pc[2 * j + 1]));
         pc += 32;
     }
-    const int nsign = int((h >> 8) & 0xffff), ngroup = int((h >> 24) & 0xffff);
     if (nsign) {
         uint32_t s = 0;
         for (int i = 0; i < nsign; ++i) {
-            const uint32_t amps = uint32_t(pc[2]);   // read first: a load under a condition is a branch
-            s ^= (idx & pc[0]) == pc[1] ? amps : 0u;
-            pc += 3;
+#pragma unroll
+            for (int k = 0; k < kTileSigns; ++k) {
+                const uint32_t amps = uint32_t(pc[3 * k + 2]);   // read first: a load under a condition is a branch
+                s ^= (idx & pc[3 * k]) == pc[3 * k + 1] ? amps : 0u;
+            }
+            pc += 3 * kTileSigns;
         }
 #pragma unroll
         for (int j = 0; j < 16; ++j) {   // all 16: a branch around each costs more
@@ -355,7 +362,6 @@ __device__ __forceinline__ Words diagonal(double (&xr)[16], double (&xi)[16], ui
             }
         }
     }
-    return pc;
 }
 
 template <typename S, int T, bool NT>
@@ -389,32 +395,33 @@ __global__ __launch_bounds__(1 << (T - 4), 4) void k_tile_pass(typename V2<S>::T
     for (int st = 0;; ++st) {
         int nops = int(pc[2] >> 32);
         pc += 3;
+        Head cur = *(const Head __attribute__((address_space(4))) *)pc;
         for (; nops > 0; --nops) {
-            const uint64_t h = pc[0];
-            ++pc;
-            const int type = int(h & 0xff);
-            if (type == kTileDiag) {
-                pc = diagonal(xr, xi, h, pc, L.idx);
-            } else if (type == kTileRotate) {
-                QS_BIT_CASES(rotate1, int((h >> 8) & 3), xr, xi, pc)
-                pc += 4;
+            // the next operation's first words are on their way while this
+            // one runs
+            const uint64_t h = cur[0];
+            const Words op = pc + 1;
+            pc += h >> 32;
+            const Head next = *(const Head __attribute__((address_space(4))) *)pc;
+            const int type = int(h) & 7, arg = int(h >> 3) & 7;
+            if (type == kTileRotate) {
+                QS_BIT_CASES(rotate1, arg, xr, xi, cur)
+            } else if (type == kTileDiag) {
+                diagonal(xr, xi, uint32_t(h), op, L.idx);
             } else if (type == kTileDense1) {
-                QS_BIT_CASES(dense1, int((h >> 8) & 3), xr, xi, pc)
-                pc += 8;
-            } else if (type == kTileCDense1) {
-                const bool on = (L.idx & pc[0]) == pc[1];
-                const uint32_t amps = uint32_t(h >> 16) & 0xffff;
-                QS_BIT_CASES(cdense1, int((h >> 8) & 3), xr, xi, pc + 2, on, amps)
-                pc += 10;
-            } else if (type == kTileX) {
-                const bool on = (L.idx & pc[0]) == pc[1];
-                const uint32_t amps = uint32_t(h >> 16) & 0xffff;
-                QS_BIT_CASES(xswap, int((h >> 8) & 3), xr, xi, on, amps)
-                pc += 2;
+                QS_BIT_CASES(dense1, arg, xr, xi, op)
+            } else if (type == kTileDense2) {
+                QS_PAIR_CASES(dense2, arg, xr, xi, op)
             } else {
-                QS_PAIR_CASES(dense2, int((h >> 8) & 7), xr, xi, pc)
-                pc += 32;
+                const bool on = (L.idx & cur[1]) == cur[2];
+                const uint32_t amps = uint32_t(h >> 8) & 0xffff;
+                if (type == kTileX) {
+                    QS_BIT_CASES(xswap, arg, xr, xi, on, amps)
+                } else {
+                    QS_BIT_CASES(cdense1, arg, xr, xi, op + 2, on, amps)
+                }
             }
+            cur = next;
         }
         if (st + 1 >= tg.n_stages) break;
         Layout<T> M;
