@@ -15,7 +15,9 @@
 // transform moves the state P times. The passes alternate between the
 // state and a scratch buffer so that the last one lands in the state.
 //
-// Passes over a 10-bit digit (every pass of a 30-qubit QFT) run on
+// Passes run on register tiles. Digits of up to 10 bits take fft_tile.hip's
+// kernel (one workgroup per tile, four on a compute unit) unless the rule in
+// run_fft finds this file's 10-bit kernels faster. Those are the persistent
 // register-tile kernels: a tile is the 1024 digit values of C columns with
 // C amplitudes = 128 bytes per row (8 complex128, 16 complex64), the
 // shortest row that a DRAM burst serves in full; rows of the top digit lie
@@ -25,7 +27,8 @@
 // transforms one tile while the next one loads into registers. The
 // register-tile kernels are described with their code below.
 //
-// Other passes (and every pass under FFT kernel options 1 and 2) use an
+// Passes on states of fewer than 10 qubits (and every pass under FFT kernel
+// options 1 and 2, and narrower digits under 3 and 5) use an
 // LDS tile of 2^r digit values x C columns (C consecutive values of the
 // lowest available bits; the 80 KB budget gives a 10-bit digit C = 4
 // complex128 or 8 complex64 columns, 64 bytes) and perform the 2^r-point
@@ -49,6 +52,7 @@
 // device code of the LDS-tile kernels lives in fft_dev.h (shared with the
 // batched kernel).
 #include "fft_dev.h"
+#include "fft_tile.h"
 
 #include <cstdlib>
 
@@ -791,9 +795,9 @@ int run_fft(qs_state *h, int q_lo, int m, int inverse)
     using C2 = typename V2<R>::T;
     const FftShape shape = fft_shape(h->dtype, h->n);
     // 1 LDS tile per workgroup, 2 streaming LDS tiles, 3 register tile per
-    // workgroup, 4 persistent register tile (the default), 5 persistent
-    // register tile with eight values per thread; passes whose digit is not
-    // 10 bits wide take the LDS-tile kernel of option 1 or 2
+    // workgroup, 4 (the default) fft_tile.hip or the persistent register tile,
+    // 5 persistent register tile with eight values per thread; under 3 and 5,
+    // passes whose digit is not 10 bits wide take the LDS tiles of option 1
     int kern = tune_value(QS_TUNE_FFT_KERNEL, h->dtype, 0, 0, tune_nbucket(h->n));
     if (kern == 0) kern = 4;
     const bool stream = kern == 2;
@@ -827,7 +831,18 @@ int run_fft(qs_state *h, int q_lo, int m, int inverse)
         }
         const size_t lds = pass_lds_bytes(pa, sizeof(C2));
         const uint64_t elems = uint64_t(1) << (pa.r + pa.cb);
-        if (reg && pa.r == kRmax && pa.cb == reg_cb) {
+        // 10-bit digits: the register-tile kernels, except where their columns
+        // would be far apart (a digit that starts inside a 128-byte line: 26
+        // qubits, digit at 0, complex64: 0.64 against 0.24 ms) and for large
+        // complex128 transforms (28 qubits: 5.81 against 5.51 ms; complex64
+        // 3.17 against 3.70)
+        constexpr int line = sizeof(C2) == 16 ? 3 : 4;
+        const bool tile = kern == 4 && fft_tile_applies(h->n, pa) &&
+                          (pa.r != kRmax || pa.cb != reg_cb || (pa.dig_lo < line && !pa.final_pass) ||
+                           (sizeof(C2) == 16 && P > 1 && h->n >= 26));
+        if (tile) {
+            if (int rc = launch_fft_tile(h, pa, src, dst)) return rc;
+        } else if (reg && pa.r == kRmax && pa.cb == reg_cb) {
             const C2 *roots = nullptr;
             if (pa.tw_bits && kern == 3) {
                 if (!h->fft_roots)

@@ -142,3 +142,21 @@ def test_diagonal_circuit(Q, O, S):
     st.set(psi0)
     st.apply_circuit(gates, 2)
     assert np.abs(st.get() - O.apply_circuit(psi0, gates)).max() < 1e-10
+
+
+@pytest.mark.parametrize("dtype", [1, 0])
+@pytest.mark.parametrize("n,lo,m", [(10, 0, 10), (10, 7, 3), (11, 0, 11), (12, 1, 1), (13, 4, 5), (13, 0, 13),
+                                    (14, 2, 9), (14, 0, 12), (15, 3, 4), (15, 0, 15), (16, 5, 7), (17, 0, 17),
+                                    (18, 0, 18), (19, 1, 18), (20, 6, 8), (21, 0, 21)])
+@pytest.mark.parametrize("inverse", [False, True])
+def test_fft_every_digit_width(Q, O, S, dtype, n, lo, m, inverse):
+    """Digits of 1 to 10 bits, one to three passes, registers at the bottom,
+    inside and at the top of the state. The error of an m-bit transform is
+    some m roundings of the norm-one state's amplitudes."""
+    psi0 = S.normal_state(n, n + m).astype(np.complex128 if dtype else np.complex64)
+    ref = O.dft_numpy(psi0.astype(np.complex128), lo, m, inverse)
+    st = Q.State(n, dtype)
+    st.set(psi0)
+    st.emulate_qft(lo, m, inverse)
+    tol = m * (2.0 ** -52 if dtype else 2.0 ** -23)
+    assert np.linalg.norm(st.get() - ref) < tol
