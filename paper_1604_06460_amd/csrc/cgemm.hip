@@ -7,16 +7,24 @@
 // Re C = Re A Re B - Im A Im B, Im C = Re A Im B + Im A Re B, so the real
 // work equals the complex work (8 flops per complex multiply-add).
 //
-// Tiling: a 256-thread workgroup owns a BM x BM tile of C (BM = 128, or 64
-// when 128-tiles would leave compute units idle); its four waves each own a
-// quarter as (BM/32) x (BM/32) MFMA tiles of 16 x 16, with real and
-// imaginary accumulators (128 values per lane at BM = 128). K advances 8
-// complex entries at a time: the A and B panels (BM x 8 each) are staged in
-// LDS as separate real and imaginary planes laid out [k][row] / [k][col],
-// so every fragment read is 16 consecutive values per quarter-wave. The
-// next panel is loaded into registers while the current one is multiplied
-// and then written to the second of two LDS buffers, so each K step needs
-// one barrier.
+// Tiling: a 256-thread workgroup owns a BM x BM tile of C (BM = 128, 64 or
+// 32); its four waves each own a quarter as (BM/32) x (BM/32) MFMA tiles of
+// 16 x 16, with real and imaginary accumulators (128 values per lane at BM =
+// 128). K advances kBK complex entries at a time (8, or 16 for BM = 32, where
+// a step of 8 is too short for its barrier): the A and B panels (BM x kBK
+// each) are staged in LDS as separate real and imaginary planes laid out
+// [k][row] / [k][col], so every fragment read is 16 consecutive values per
+// quarter-wave. The next panel is loaded into registers while the current one
+// is multiplied and then written to the second of two LDS buffers, so each K
+// step needs one barrier.
+//
+// What bounds it: the matrix cores. One workgroup per compute unit (BM = 64
+// at 1024 x 1024) has one wave per SIMD and nothing to run while it loads,
+// stores and waits at the barrier: 180 us for a product of 1024 in complex128
+// (109 us at the peak rate), and as much with half the columns, on half the
+// compute units. Tiles of 32 have up to four waves per SIMD; their panels are
+// swizzled over the LDS banks, which at BM = 64 costs more than it gives
+// (11 qubits, 11 bits: 18.4 -> 19.7 ms).
 //
 // MFMA lane layouts (16x16x4, checked on the device): A[i][k] in lane
 // i + 16k and B[k][j] in lane j + 16k for both precisions; D[i][j] is in
@@ -27,7 +35,7 @@
 namespace qs {
 namespace {
 
-constexpr int kBK = 8, kThreads = 256;
+constexpr int kThreads = 256;
 
 template <typename R> struct Cx;
 template <> struct Cx<double> {
@@ -56,7 +64,7 @@ __device__ __forceinline__ uint64_t col_off(const ColMap &m, uint64_t c)
 }
 
 template <typename R, bool CONJ_A, int BM>
-__global__ __launch_bounds__(kThreads, BM == 128 ? 1 : 2) void k_cgemm(const typename Cx<R>::T *__restrict__ A, int64_t lda, int M,
+__global__ __launch_bounds__(kThreads, BM == 128 ? 1 : BM == 64 ? 2 : 4) void k_cgemm(const typename Cx<R>::T *__restrict__ A, int64_t lda, int M,
                                                         int K, const typename Cx<R>::T *__restrict__ B, ColMap bm,
                                                         typename Cx<R>::T *__restrict__ C, ColMap cm, uint64_t ncols)
 {
@@ -64,8 +72,15 @@ __global__ __launch_bounds__(kThreads, BM == 128 ? 1 : 2) void k_cgemm(const typ
     using V4 = typename Cx<R>::V4;
     constexpr int kBM = BM, kBN = BM;
     constexpr int TX = BM / 32;          // MFMA tiles per wave and direction
-    constexpr int Q = BM / 32;           // panel elements per thread
+    constexpr int kBK = BM == 32 ? 16 : 8;
+    constexpr int Q = BM * kBK / kThreads;   // panel elements per thread
     constexpr int TPR = kBK / Q;         // threads per k-contiguous panel row
+    constexpr int TPK = BM / Q;          // threads per panel column of A
+    // place of entry (k, i) of a panel in LDS; at BM = 32 two rows k would
+    // share their banks in a fragment read, and eight in a write
+    auto at = [](int k, int i) {
+        return k * BM + (BM == 32 ? i ^ ((k & 1) << 4) ^ ((k >> 1) << 2) : i);
+    };
     // two panel buffers: the next panel is written while the current one is
     // read, so one barrier per K step suffices
     __shared__ R a_re[2][kBK * kBM], a_im[2][kBK * kBM], b_re[2][kBK * kBN], b_im[2][kBK * kBN];
@@ -89,7 +104,7 @@ __global__ __launch_bounds__(kThreads, BM == 128 ? 1 : 2) void k_cgemm(const typ
 
     auto load_panel = [&](int k0) {
         if constexpr (!CONJ_A) {
-            const int ak = t >> 5, ai = (t & 31) * Q;
+            const int ak = t / TPK, ai = (t % TPK) * Q;
             const int k = k0 + ak;
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
@@ -113,24 +128,24 @@ __global__ __launch_bounds__(kThreads, BM == 128 ? 1 : 2) void k_cgemm(const typ
     };
     auto store_panel = [&](int buf) {
         if constexpr (!CONJ_A) {
-            const int ak = t >> 5, ai = (t & 31) * Q;
+            const int ak = t / TPK, ai = (t % TPK) * Q;
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
-                a_re[buf][ak * kBM + ai + q] = ra[q].x;
-                a_im[buf][ak * kBM + ai + q] = ra[q].y;
+                a_re[buf][at(ak, ai + q)] = ra[q].x;
+                a_im[buf][at(ak, ai + q)] = ra[q].y;
             }
         } else {
             const int ai = t / TPR, ak = (t % TPR) * Q;
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
-                a_re[buf][(ak + q) * kBM + ai] = ra[q].x;
-                a_im[buf][(ak + q) * kBM + ai] = -ra[q].y;
+                a_re[buf][at(ak + q, ai)] = ra[q].x;
+                a_im[buf][at(ak + q, ai)] = -ra[q].y;
             }
         }
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-            b_re[buf][(bk + q) * kBN + bj] = rb[q].x;
-            b_im[buf][(bk + q) * kBN + bj] = rb[q].y;
+            b_re[buf][at(bk + q, bj)] = rb[q].x;
+            b_im[buf][at(bk + q, bj)] = rb[q].y;
         }
     };
 
@@ -156,14 +171,14 @@ __global__ __launch_bounds__(kThreads, BM == 128 ? 1 : 2) void k_cgemm(const typ
             R ar[TX], ai[TX], br[TX], bi[TX], nai[TX];
 #pragma unroll
             for (int x = 0; x < TX; ++x) {
-                ar[x] = a_re[cur][(ks + fk) * kBM + wr + 16 * x + fi];
-                ai[x] = a_im[cur][(ks + fk) * kBM + wr + 16 * x + fi];
+                ar[x] = a_re[cur][at(ks + fk, wr + 16 * x + fi)];
+                ai[x] = a_im[cur][at(ks + fk, wr + 16 * x + fi)];
                 nai[x] = -ai[x];
             }
 #pragma unroll
             for (int y = 0; y < TX; ++y) {
-                br[y] = b_re[cur][(ks + fk) * kBN + wc + 16 * y + fi];
-                bi[y] = b_im[cur][(ks + fk) * kBN + wc + 16 * y + fi];
+                br[y] = b_re[cur][at(ks + fk, wc + 16 * y + fi)];
+                bi[y] = b_im[cur][at(ks + fk, wc + 16 * y + fi)];
             }
             // four sweeps over the tiles, so that consecutive updates of one
             // accumulator are 2 TX TY instructions apart (no dependent issue)
@@ -221,23 +236,30 @@ void launch_tile(hipStream_t s, bool conj_a, const void *A, int64_t lda, int M, 
 
 }  // namespace
 
-// 128 x 128 tiles when they give every compute unit at least two; 64 x 64
-// tiles (four times as many workgroups, two per compute unit) otherwise.
+// The largest of 128, 64 and 32 that is no larger than A needs and whose tiles
+// give every compute unit at least two workgroups. Phase estimation with
+// controlled powers, 64 as the smallest tile against this: m = 8, 8 bits,
+// complex128 0.96 -> 0.48 ms; m = 9, 9 bits 2.45 -> 1.46; m = 10, 10 bits
+// 4.5 -> 3.5; complex64 m = 9, 9 bits 2.46 -> 1.62; with m = 11, 11 bits tiles
+// of 64 already suffice (18.6 and 18.4).
 int launch_cgemm(hipStream_t s, int dtype, bool conj_a, const void *A, int64_t lda, int M, int K, const void *B,
                  ColMap bm, void *C, ColMap cm, uint64_t ncols)
 {
     if (M < 1 || K < 1 || ncols == 0) return QS_OK;
-    const uint64_t big = ((ncols + 127) / 128) * uint64_t((M + 127) / 128);
-    const int bmt = big >= 2 * uint64_t(device_cus()) ? 128 : 64;
+    int bmt = 128;
+    while (bmt > 32 && (bmt >= 2 * M || ((ncols + bmt - 1) / bmt) * uint64_t((M + bmt - 1) / bmt) < 2 * uint64_t(device_cus())))
+        bmt /= 2;
     const uint64_t gx = (ncols + bmt - 1) / bmt;
     if (gx > 0x7fffffffull) return fail(QS_EUNSUPPORTED, "complex GEMM with %llu columns", (unsigned long long)ncols);
     const dim3 grid(unsigned(gx), unsigned((M + bmt - 1) / bmt));
     if (dtype == QS_C128) {
         if (bmt == 128) launch_tile<double, 128>(s, conj_a, A, lda, M, K, B, bm, C, cm, ncols, grid);
-        else launch_tile<double, 64>(s, conj_a, A, lda, M, K, B, bm, C, cm, ncols, grid);
+        else if (bmt == 64) launch_tile<double, 64>(s, conj_a, A, lda, M, K, B, bm, C, cm, ncols, grid);
+        else launch_tile<double, 32>(s, conj_a, A, lda, M, K, B, bm, C, cm, ncols, grid);
     } else {
         if (bmt == 128) launch_tile<float, 128>(s, conj_a, A, lda, M, K, B, bm, C, cm, ncols, grid);
-        else launch_tile<float, 64>(s, conj_a, A, lda, M, K, B, bm, C, cm, ncols, grid);
+        else if (bmt == 64) launch_tile<float, 64>(s, conj_a, A, lda, M, K, B, bm, C, cm, ncols, grid);
+        else launch_tile<float, 32>(s, conj_a, A, lda, M, K, B, bm, C, cm, ncols, grid);
     }
     QS_HIP(hipGetLastError());
     return QS_OK;

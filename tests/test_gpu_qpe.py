@@ -81,6 +81,30 @@ def test_controlled_unitary_many_batches_matrix_core(Q, O, S, dtype):
 
 
 @pytest.mark.parametrize("dtype", [1, 0])
+@pytest.mark.parametrize("m,n", [(5, 13), (6, 21), (6, 22), (7, 21), (7, 22), (7, 24), (9, 18)])
+def test_controlled_unitary_every_tile_size(Q, S, dtype, m, n):
+    """Registers of 2^m and columns on both sides of every tile size's rule,
+    against the product in FP64 on the device."""
+    torch = pytest.importorskip("torch")
+    u = Q.Unitary(_circuit(S, m, 5 + m), m)
+    U = torch.from_numpy(u.get()).cuda()
+    g = torch.Generator(device="cuda").manual_seed(n)
+    ctype, eps = (torch.complex128, 1.2e-16) if dtype else (torch.complex64, 6e-8)
+    psi = torch.randn(1 << n, dtype=ctype, device="cuda", generator=g) / 2.0 ** (n / 2)
+    want = psi.to(torch.complex128).reshape(2, -1, 1 << m)
+    want = torch.stack([want[0], want[1] @ U.T.contiguous()]).reshape(-1)
+    buf = psi.clone()
+    torch.cuda.synchronize()
+    st = Q.State(n, dtype, device_buf=buf.data_ptr())
+    u.apply_controlled(st, n - 1)
+    st.sync()
+    # an entry is a sum of 4 * 2^m real products of numbers below max |psi|
+    assert (buf - want).abs().max().item() <= 4 * 2 ** m * eps * psi.abs().max().item()
+    st.free()
+    u.free()
+
+
+@pytest.mark.parametrize("dtype", [1, 0])
 def test_controlled_unitary_every_control_position(Q, O, S, dtype):
     m, n = 3, 11
     gates = _circuit(S, m, 3)
