@@ -147,9 +147,22 @@ __device__ __forceinline__ void row_dot(const R *__restrict__ row, const C2 (&v)
     }
 }
 
-template <typename R, int K, typename IT, int NT>
+// A small matrix travels with the launch: staging it took a copy of 1.9 us
+// and its submission for every gate, and a cast as well for complex64, next
+// to a kernel of 2.8 us on 16 qubits. The entries are read through the same
+// scalar loads. 480 gates of one and two qubits on 16 qubits: 4.31 -> 3.39 ms
+// in complex128; 14 qubits in complex64 4.89 -> 3.04 ms. Wider gates, and
+// blocks of programs, read theirs from device memory.
+template <typename R, int K> struct MatArg {
+    R v[2 << (2 * K)];
+};
+constexpr int kMatArgBits = 2;
+template <typename R> __device__ __forceinline__ const R *entries(const R *m) { return m; }
+template <typename R, int K> __device__ __forceinline__ const R *entries(const MatArg<R, K> &m) { return m.v; }
+
+template <typename R, int K, typename IT, int NT, typename M>
 __global__ __launch_bounds__(kBlock) void k_dense(typename V2<R>::T *__restrict__ psi,
-                                                  const R *__restrict__ mat, IT n_groups,
+                                                  const M mat, IT n_groups,
                                                   FixArgs fx, OffArgs<(1 << K)> off)
 {
     using C2 = typename V2<R>::T;
@@ -164,7 +177,7 @@ __global__ __launch_bounds__(kBlock) void k_dense(typename V2<R>::T *__restrict_
 #pragma unroll 1
         for (int j = 0; j < D; ++j) {
             R re = R(0), im = R(0);
-            row_dot<R, C2, D>(mat + 2 * j * D, v, re, im);
+            row_dot<R, C2, D>(entries(mat) + 2 * j * D, v, re, im);
             store_amp(p + off.o[j], C2{re, im}, NT);
         }
     }
@@ -194,9 +207,9 @@ __device__ __forceinline__ int lds_slot(int p)
     return p ^ ((p / SW) & (SW - 1));
 }
 
-template <typename R, int K, typename IT, int NT>
+template <typename R, int K, typename IT, int NT, typename M>
 __global__ __launch_bounds__(64) void k_dense_lds(typename V2<R>::T *__restrict__ psi,
-                                                  const R *__restrict__ mat, IT n_tiles,
+                                                  const M mat, IT n_tiles,
                                                   FixArgs fx, OffArgs<(1 << K)> offl,
                                                   LdsArgs<(1 << K)> la)
 {
@@ -220,7 +233,7 @@ __global__ __launch_bounds__(64) void k_dense_lds(typename V2<R>::T *__restrict_
 #pragma unroll 1
         for (int j = 0; j < D; ++j) {
             R re = R(0), im = R(0);
-            row_dot<R, C2, D>(mat + 2 * j * D, v, re, im);
+            row_dot<R, C2, D>(entries(mat) + 2 * j * D, v, re, im);
             tile[lds_slot<C2>(lp | la.offc[j])] = C2{re, im};
         }
         __syncthreads();
@@ -250,9 +263,9 @@ struct TileArgs {
     int offc[1 << K];    // tile-index offset of local index j (bit m <-> target m)
 };
 
-template <typename R, int K, typename IT, int NT>
+template <typename R, int K, typename IT, int NT, typename M>
 __global__ __launch_bounds__(256) void k_dense_tile(typename V2<R>::T *__restrict__ psi,
-                                                    const R *__restrict__ mat, IT n_tiles,
+                                                    const M mat, IT n_tiles,
                                                     FixArgs ft, TileArgs<K> ta)
 {
     using C2 = typename V2<R>::T;
@@ -276,7 +289,7 @@ __global__ __launch_bounds__(256) void k_dense_tile(typename V2<R>::T *__restric
         for (int i = 0; i < 10; ++i) o |= IT((e >> i) & 1) << ta.tb[i];
         off[u] = o;
     }
-    const R *rows = mat + 2 * (4 * g) * D;
+    const R *rows = entries(mat) + 2 * (4 * g) * D;
     const IT t = xcd_order<IT, kXcdRunDense>(blockIdx.x, gridDim.x);
     if (t >= n_tiles) return;   // whole workgroup: the barriers below stay uniform
     C2 *p = psi + expand<IT>(t, ft);
@@ -596,8 +609,9 @@ void make_off(const GateDesc &d, OffArgs<D> &o)
     }
 }
 
-template <typename R, typename IT, int K>
-int dense_k(qs_state *h, const GateDesc &d, const void *dmat)
+// M: const R * (device memory) or MatArg
+template <typename R, typename IT, int K, typename M>
+int dense_k(qs_state *h, const GateDesc &d, const M m)
 {
     using C2 = typename V2<R>::T;
     constexpr int D = 1 << K;
@@ -609,7 +623,6 @@ int dense_k(qs_state *h, const GateDesc &d, const void *dmat)
     make_off<D>(d, off);
     const IT n_groups = IT(h->dim() >> np);
     C2 *psi = static_cast<C2 *>(h->psi);
-    const R *m = static_cast<const R *>(dmat);
     int mint = 64;
     for (int i = 0; i < K; ++i) mint = std::min(mint, d.targets[i]);
     // tuned choices for this (dtype, k, target class, n bucket); 0 = default
@@ -624,7 +637,7 @@ int dense_k(qs_state *h, const GateDesc &d, const void *dmat)
     // 5- and 6-qubit blocks on complex64 states: batched GEMM on the matrix
     // cores
     if constexpr (sizeof(R) == 4 && K >= 5) {
-        if ((path == 0 || path == 3) && mfma_applicable(h, d)) return launch_dense_mfma(h, d, dmat);
+        if ((path == 0 || path == 3) && mfma_applicable(h, d)) return launch_dense_mfma(h, d, m);
     }
     // complex128 blocks of 2 to 4 qubits on states of 20 qubits or more
     // default to the workgroup-shared 1024-amplitude tile
@@ -654,7 +667,7 @@ int dense_k(qs_state *h, const GateDesc &d, const void *dmat)
             if (uint64_t(n_tiles) > 0x7fffffffull) return fail(QS_EUNSUPPORTED, "tile grid of %llu workgroups", (unsigned long long)n_tiles);
             const unsigned grid = unsigned(n_tiles);   // one tile per workgroup; no grid cap
             with_nt(nt, [&](auto c) {
-                hipLaunchKernelGGL((k_dense_tile<R, K, IT, decltype(c)::value>), dim3(grid), dim3(256), 0,
+                hipLaunchKernelGGL((k_dense_tile<R, K, IT, decltype(c)::value, M>), dim3(grid), dim3(256), 0,
                                    h->stream, psi, m, n_tiles, ft, ta);
             });
             QS_HIP(hipGetLastError());
@@ -714,7 +727,7 @@ int dense_k(qs_state *h, const GateDesc &d, const void *dmat)
                                        n_tiles, ft, offl, la);
             } else if constexpr (lds_capable) {
                 with_nt(nt, [&](auto c) {
-                    hipLaunchKernelGGL((k_dense_lds<R, K, IT, decltype(c)::value>), dim3(grid), dim3(64), 0,
+                    hipLaunchKernelGGL((k_dense_lds<R, K, IT, decltype(c)::value, M>), dim3(grid), dim3(64), 0,
                                        h->stream, psi, m, n_tiles, ft, offl, la);
                 });
             }
@@ -728,7 +741,7 @@ int dense_k(qs_state *h, const GateDesc &d, const void *dmat)
                            dim3(kBlock), 0, h->stream, psi, m, n_groups, fx, off);
     } else {
         with_nt(nt, [&](auto c) {
-            hipLaunchKernelGGL((k_dense<R, K, IT, decltype(c)::value>), dim3(capped(grid_for(n_groups))),
+            hipLaunchKernelGGL((k_dense<R, K, IT, decltype(c)::value, M>), dim3(capped(grid_for(n_groups))),
                                dim3(kBlock), 0, h->stream, psi, m, n_groups, fx, off);
         });
     }
@@ -739,15 +752,31 @@ int dense_k(qs_state *h, const GateDesc &d, const void *dmat)
 template <typename R, typename IT>
 int dense_dispatch(qs_state *h, const GateDesc &d, const void *dmat)
 {
+    const R *m = static_cast<const R *>(dmat);
     switch (d.k) {
-    case 1: return dense_k<R, IT, 1>(h, d, dmat);
-    case 2: return dense_k<R, IT, 2>(h, d, dmat);
-    case 3: return dense_k<R, IT, 3>(h, d, dmat);
-    case 4: return dense_k<R, IT, 4>(h, d, dmat);
-    case 5: return dense_k<R, IT, 5>(h, d, dmat);
-    case 6: return dense_k<R, IT, 6>(h, d, dmat);
+    case 1: return dense_k<R, IT, 1>(h, d, m);
+    case 2: return dense_k<R, IT, 2>(h, d, m);
+    case 3: return dense_k<R, IT, 3>(h, d, m);
+    case 4: return dense_k<R, IT, 4>(h, d, m);
+    case 5: return dense_k<R, IT, 5>(h, d, m);
+    case 6: return dense_k<R, IT, 6>(h, d, m);
     default: return fail(QS_EUNSUPPORTED, "dense gate width %d", d.k);
     }
+}
+
+// The matrix in host memory, k <= kMatArgBits.
+template <typename R, typename IT, int K>
+int dense_host_k(qs_state *h, const GateDesc &d, const double *hmat)
+{
+    MatArg<R, K> m;
+    for (int i = 0; i < 2 << (2 * K); ++i) m.v[i] = R(hmat[i]);
+    return dense_k<R, IT, K>(h, d, m);
+}
+
+template <typename R, typename IT>
+int dense_host_dispatch(qs_state *h, const GateDesc &d, const double *hmat)
+{
+    return d.k == 1 ? dense_host_k<R, IT, 1>(h, d, hmat) : dense_host_k<R, IT, 2>(h, d, hmat);
 }
 
 template <typename R, typename IT, int K>
@@ -1084,7 +1113,15 @@ int enqueue_gate(qs_state *h, const GateDesc &din, const double *hmat)
     default:
         break;
     }
-    // dense and diagonal kernels read the matrix from device memory
+    if (d.cls == GC_DENSE && d.k <= kMatArgBits) {
+        const bool small = h->n <= 31;
+        if (h->dtype == QS_C128)
+            return small ? dense_host_dispatch<double, uint32_t>(h, d, hmat)
+                         : dense_host_dispatch<double, uint64_t>(h, d, hmat);
+        return small ? dense_host_dispatch<float, uint32_t>(h, d, hmat)
+                     : dense_host_dispatch<float, uint64_t>(h, d, hmat);
+    }
+    // wider dense and diagonal kernels read the matrix from device memory
     const size_t count = 2 * D * D;
     void *dm = nullptr;
     if (int rc = h->stage.put(h->stream, hmat, count * sizeof(double), &dm)) return rc;

@@ -448,3 +448,27 @@ def test_structured_gates_inside_a_cache_line(Q, O, S, dtype):
         else:
             assert np.abs(got - ref).max() < (1e-13 if dtype == 1 else 2e-6), g.name
         st.free()
+
+
+@pytest.mark.parametrize("dtype", [1, 0])
+@pytest.mark.parametrize("n", [3, 9, 20])
+def test_matrix_as_argument_equals_staged(Q, S, dtype, n):
+    """A dense gate whose matrix travels with the launch gives the bits of the
+    same sweep with the matrix in device memory (a program's block)."""
+    rng = np.random.default_rng(60 + n)
+    psi0 = S.normal_state(n, 61)
+    for targets in [(0,), (1,), (n - 1,), (0, 1), (0, n - 1), (1, n - 2), (n - 2, n - 1)]:
+        if len(set(targets)) < len(targets) or list(targets) != sorted(targets):
+            continue
+        d = 1 << len(targets)
+        m, _ = np.linalg.qr(rng.standard_normal((d, d)) + 1j * rng.standard_normal((d, d)))
+        a, b = Q.State(n, dtype), Q.State(n, dtype)
+        a.set(psi0)
+        b.set(psi0)
+        a.apply_gate(targets, m)
+        prog = b.compile([S.Gate(targets, m)], len(targets))
+        b.run_range(prog, 0, 1)
+        assert np.array_equal(a.get(), b.get()), targets
+        prog.free()
+        a.free()
+        b.free()
