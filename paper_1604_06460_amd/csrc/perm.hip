@@ -573,12 +573,7 @@ int emulate_modmul(qs_state *h, const qs_perm *p)
 {
     if (int rc = ensure_scratch(h)) return rc;
     const int cnt = 1 << p->c;
-    void *dinv = nullptr;
-    if (int rc = h->stage.reserve(h->stream, sizeof(uint64_t) * size_t(cnt), &dinv)) return rc;
     const uint64_t mu = barrett_mu(p->N);
-    hipLaunchKernelGGL(k_inv_powers, dim3((cnt + kThreads - 1) / kThreads), dim3(kThreads), 0,
-                       h->stream, p->a, p->N, mu, cnt, static_cast<uint64_t *>(dinv));
-    QS_HIP(hipGetLastError());
     ModmulArgs ma{p->work_lo, p->w, p->ctrl_lo, p->c, p->N, mu};
     // tiled gather: work register at the bottom of the index, a modulus
     // well above the row counts, at most 2^12 control values (one row table
@@ -599,6 +594,11 @@ int emulate_modmul(qs_state *h, const qs_perm *p)
         QS_HIP(hipGetLastError());
         return adopt_scratch(h);
     }
+    void *dinv = nullptr;
+    if (int rc = h->stage.reserve(h->stream, sizeof(uint64_t) * size_t(cnt), &dinv)) return rc;
+    hipLaunchKernelGGL(k_inv_powers, dim3((cnt + kThreads - 1) / kThreads), dim3(kThreads), 0,
+                       h->stream, p->a, p->N, mu, cnt, static_cast<uint64_t *>(dinv));
+    QS_HIP(hipGetLastError());
     const bool small = h->n <= 31;
     const uint64_t *inv = static_cast<const uint64_t *>(dinv);
     if (h->dtype == QS_C128) {
