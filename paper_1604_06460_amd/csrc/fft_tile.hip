@@ -15,9 +15,8 @@
 //
 // Twiddles: each thread forms its own roots by FP64 sincospi on exponents
 // that are reduced in integers; a value's twiddle is the product of two.
-// Complex64
-// tiles are computed in FP64 between loads, exchanges and stores: without
-// packed FP32 that is the same number of instructions.
+// Complex64 tiles are computed in FP64 between loads, exchanges and stores:
+// without packed FP32 that is the same number of instructions.
 //
 // What bounds it: memory. Four workgroups of four waves share a compute unit,
 // so loads of one tile overlap with the arithmetic of others, without the

@@ -11,7 +11,7 @@ struct qs_circuit;
 
 namespace qs {
 
-constexpr int kTileBitsMin = 10, kTileBitsMax = 13;   // qubits of a tile
+constexpr int kTileBitsMin = 10, kTileBitsMax = 12;   // qubits of a tile
 
 // A pass in the word stream: per stage three words of layout, then its
 // operations.
