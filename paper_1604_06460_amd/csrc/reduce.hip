@@ -94,19 +94,33 @@ __global__ __launch_bounds__(kThreads) void k_pauli(const typename V2<R>::T *__r
     }
 }
 
-// Fixed-order final sum of `count` tuples of width w; out may be mapped host
-// memory.
-__global__ void k_finish(const double *__restrict__ partial, int count, int w,
-                         double *__restrict__ out)
+// Fixed-order sums over `count` tuples of width W, valid in thread 0. The
+// columns are read together: one after the other they wait for memory twice
+// (2048 pairs: 4.1 -> 4.1 us).
+template <int W>
+__device__ __forceinline__ void finish_sums(const double *__restrict__ partial, int count, double (&s)[W])
 {
-    __shared__ double sh[kThreads / 64];
-    for (int c = 0; c < w; ++c) {
-        double s = 0.0;
+    __shared__ double sh[W][kThreads / 64];
+#pragma unroll
+    for (int c = 0; c < W; ++c) s[c] = 0.0;
 #pragma unroll 8
-        for (int i = threadIdx.x; i < count; i += kThreads) s += partial[size_t(i) * w + c];
-        s = block_sum(s, sh);
-        if (threadIdx.x == 0) out[c] = s;
-    }
+    for (int i = threadIdx.x; i < count; i += kThreads)
+#pragma unroll
+        for (int c = 0; c < W; ++c) s[c] += partial[size_t(i) * W + c];
+#pragma unroll
+    for (int c = 0; c < W; ++c) s[c] = block_sum(s[c], sh[c]);
+}
+
+// out may be mapped host memory
+template <int W>
+__global__ __launch_bounds__(kThreads) void k_finish(const double *__restrict__ partial, int count,
+                                                     double *__restrict__ out)
+{
+    double s[W];
+    finish_sums<W>(partial, count, s);
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int c = 0; c < W; ++c) out[c] = s[c];
 }
 
 struct QArgs {
@@ -337,15 +351,11 @@ __global__ void k_gather_amps(const typename V2<R>::T *__restrict__ psi,
 
 // Fixed-order final sum of the Pauli partials (as k_finish), times
 // i^{popcount(y)} (y_pow = popcount(y) mod 4), written to device memory.
-__global__ void k_finish_pauli(const double *__restrict__ partial, int count, int y_pow, double *__restrict__ out)
+__global__ __launch_bounds__(kThreads) void k_finish_pauli(const double *__restrict__ partial, int count, int y_pow,
+                                                           double *__restrict__ out)
 {
-    __shared__ double sh[kThreads / 64];
     double s[2];
-    for (int c = 0; c < 2; ++c) {
-        double v = 0.0;
-        for (int i = threadIdx.x; i < count; i += kThreads) v += partial[size_t(i) * 2 + c];
-        s[c] = block_sum(v, sh);
-    }
+    finish_sums<2>(partial, count, s);
     if (threadIdx.x == 0) {
         double r = s[0], im = s[1];
         switch (y_pow) {
@@ -404,7 +414,8 @@ unsigned red_grid(uint64_t items)
 int finish_to_host(qs_state *h, int count, int w, double *out)
 {
     if (int rc = ensure_host_out(h, sizeof(double) * size_t(w))) return rc;
-    hipLaunchKernelGGL(k_finish, dim3(1), dim3(kThreads), 0, h->stream, h->partials, count, w, h->host_out);
+    hipLaunchKernelGGL(w == 1 ? k_finish<1> : k_finish<2>, dim3(1), dim3(kThreads), 0, h->stream, h->partials, count,
+                       h->host_out);
     QS_HIP(hipGetLastError());
     QS_HIP(hipStreamSynchronize(h->stream));
     for (int c = 0; c < w; ++c) out[c] = h->host_out[c];
