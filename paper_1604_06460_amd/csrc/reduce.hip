@@ -95,8 +95,10 @@ __global__ __launch_bounds__(kThreads) void k_pauli(const typename V2<R>::T *__r
 }
 
 // Fixed-order sums over `count` tuples of width W, valid in thread 0. The
-// columns are read together: one after the other they wait for memory twice
-// (2048 pairs: 4.1 -> 4.1 us).
+// columns are read together, in one pass over the tuples: an expectation of a
+// 24-qubit complex64 state 35.9 -> 35.3 us, of 20 qubits 19.1 -> 18.4, of 14
+// (few tuples) 16.6 -> 16.4 from call to result. Kernel traces do not resolve
+// it (4.1 us before and after).
 template <int W>
 __device__ __forceinline__ void finish_sums(const double *__restrict__ partial, int count, double (&s)[W])
 {
