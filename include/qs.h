@@ -189,8 +189,32 @@ int qs_plan_fusion(const qs_circuit *c, int n_qubits, int max_k, int *n_blocks,
  * any handle of the same qubit count, any number of times. */
 int qs_compile(qs_handle h, const qs_circuit *c, int max_k, qs_program *out);
 
+/* How the library would apply a circuit as passes over tiles of the state
+ * (each pass reads and writes the state once and applies many gates), and
+ * whether it would: qs_run_program and qs_apply_circuit compare the estimated
+ * cost of the passes with that of the fused blocks. */
+typedef struct qs_pass_plan {
+    int n_passes;        /* reads and writes of the whole state */
+    int n_stages;        /* exchanges of register qubits, over all passes */
+    int n_alone;         /* gates that no pass takes: blocks of their own */
+    int ops[6];          /* operations of the passes: general one-qubit, the
+                            same under controls, X, two-qubit, real
+                            one-qubit, diagonal */
+    double cost;         /* estimated time, in sweeps over the state */
+    double block_cost;   /* the same for the blocks */
+    int program;         /* 1 if qs_run_program takes the passes */
+    int circuit;         /* 1 if qs_apply_circuit takes them */
+} qs_pass_plan;
+
+/* Host-only, like qs_plan_fusion: the pass plan of a circuit for states of
+ * n_qubits qubits and the dtype, against blocks of at most max_k qubits. On
+ * states too small for a tile every field but block_cost is zero. */
+int qs_plan_passes(const qs_circuit *c, int n_qubits, int dtype, int max_k, qs_pass_plan *out);
+
 /* Number of blocks and, if block_k != NULL, their widths; amp_moves_per_run:
- * the amplitude reads plus writes one run must make. A dense block reads and
+ * the amplitude reads plus writes that a run block by block must make (a run
+ * by passes makes 2^(n+1) for each of qs_plan_passes's passes, and those of
+ * its gates alone). A dense block reads and
  * writes all 2^n amplitudes; a diagonal block only those whose entry is not
  * exactly one (a conditional phase shift changes only the amplitudes that
  * carry its phase, Sec. III-B), and a block whose diagonal is all ones
@@ -201,7 +225,7 @@ int qs_compile(qs_handle h, const qs_circuit *c, int max_k, qs_program *out);
  * count. */
 int qs_program_info(qs_program p, int *n_blocks, int *block_k, double *amp_moves_per_run);
 
-/* How block b runs (Sec. II sweep vs Sec. III-B's touched-only phases):
+/* How block b runs when the program runs block by block (Sec. II sweep vs Sec. III-B's touched-only phases):
  * *kind = QS_BLOCK_DENSE (one sweep of the whole state), QS_BLOCK_DIAGONAL
  * (only the target patterns whose entry is not one are swept: one phase
  * launch for a single such entry, else one launch per distinct pattern of

@@ -236,11 +236,11 @@ int run_steps(qs_state *h, const qs_program_t *p)
     return QS_OK;
 }
 
-// Arguments of qs_compile and qs_apply_circuit.
-int check_circuit(const qs_state *h, const qs_circuit *c, int max_k)
+// Arguments of qs_compile, qs_apply_circuit and qs_plan_passes.
+int check_circuit(int n, const qs_circuit *c, int max_k)
 {
     if (max_k < 1 || max_k > QS_MAX_K) return fail(QS_EINVAL, "max_k=%d outside [1, %d]", max_k, QS_MAX_K);
-    if (int rc = validate_circuit(c, h->n)) return rc;
+    if (int rc = validate_circuit(c, n)) return rc;
     for (int g = 0; g < c->n_gates; ++g) {
         const uint64_t cm = c->ctrl_mask ? c->ctrl_mask[g] : 0;
         if (c->k[g] + __builtin_popcountll(cm) > QS_MAX_K)
@@ -251,7 +251,7 @@ int check_circuit(const qs_state *h, const qs_circuit *c, int max_k)
 
 // Estimated time of a plan's blocks, in sweeps. A block of diagonal gates
 // sweeps only what it changes, a quarter of the state for a CZ.
-double blocks_cost(const qs_state *h, const qs_circuit *c, const Plan &p)
+double blocks_cost(size_t amp_bytes, const qs_circuit *c, const Plan &p)
 {
     std::vector<char> diag(size_t(std::max(0, c->n_gates)));
     const double *m = c->matrices;
@@ -265,9 +265,23 @@ double blocks_cost(const qs_state *h, const qs_circuit *c, const Plan &p)
     for (size_t b = 0; b < p.block_gates.size(); ++b) {
         bool all = true;
         for (int g : p.block_gates[b]) all = all && diag[size_t(g)];
-        cost += all ? 0.25 : dense_cost(h->amp_bytes(), int(p.block_qubits[b].size()));
+        cost += all ? 0.25 : dense_cost(amp_bytes, int(p.block_qubits[b].size()));
     }
     return cost;
+}
+
+constexpr size_t kStageBytes = size_t(8) << 20;
+
+// Programs of up to 13 qubits (two tiles) always run by their blocks: on
+// such states a run in ranges gives the bits of one whole run.
+bool program_by_passes(int n, const TilePlan &t, double block_cost) { return n > 13 && t.cost < block_cost; }
+
+// A circuit that runs once: passes need no composed blocks, their words go
+// through the staging ring and nothing is allocated. A plan with gates of
+// their own, which would stage matrices over the words, is compiled.
+bool staged_by_passes(const TilePlan &t)
+{
+    return t.steps.size() == t.passes.size() && !t.steps.empty() && t.words.size() * sizeof(uint64_t) <= kStageBytes;
 }
 
 }  // namespace
@@ -297,7 +311,7 @@ int qs_alloc(int n_qubits, int dtype, void *device_buf, void *hip_stream, qs_han
         delete h;
         return fail(QS_EDEVICE, "no HIP device");
     }
-    if (int rc = h->stage.init(size_t(8) << 20)) {
+    if (int rc = h->stage.init(kStageBytes)) {
         delete h;
         return rc;
     }
@@ -479,13 +493,38 @@ int qs_plan_fusion(const qs_circuit *c, int n_qubits, int max_k, int *n_blocks, 
     return QS_OK;
 }
 
+int qs_plan_passes(const qs_circuit *c, int n_qubits, int dtype, int max_k, qs_pass_plan *out)
+{
+    clear_error();
+    if (!out) return fail(QS_EINVAL, "NULL output plan");
+    if (n_qubits < 1 || n_qubits > QS_MAX_QUBITS)
+        return fail(QS_EINVAL, "n_qubits=%d outside [1, %d]", n_qubits, QS_MAX_QUBITS);
+    if (dtype != QS_C64 && dtype != QS_C128) return fail(QS_EINVAL, "dtype=%d", dtype);
+    if (int rc = check_circuit(n_qubits, c, max_k)) return rc;
+    const size_t amp = dtype == QS_C128 ? 16 : 8;
+    Plan p;
+    if (int rc = plan_fusion(n_qubits, c->n_gates, c->k, c->targets, c->ctrl_mask, max_k, p, far_qubit(amp))) return rc;
+    *out = qs_pass_plan();
+    out->block_cost = blocks_cost(amp, c, p);
+    TilePlan t;
+    if (!plan_tiles(n_qubits, amp, c, t)) return QS_OK;
+    out->n_passes = int(t.passes.size());
+    out->n_stages = t.n_stages;
+    out->n_alone = int(t.steps.size() - t.passes.size());
+    std::copy_n(t.ops, 6, out->ops);
+    out->cost = t.cost;
+    out->program = program_by_passes(n_qubits, t, out->block_cost);
+    out->circuit = staged_by_passes(t) ? t.cost < out->block_cost : out->program;
+    return QS_OK;
+}
+
 int qs_compile(qs_handle h, const qs_circuit *c, int max_k, qs_program *out)
 {
     clear_error();
     if (int rc = check_handle(h)) return rc;
     if (!out) return fail(QS_EINVAL, "NULL output program");
     *out = nullptr;
-    if (int rc = check_circuit(h, c, max_k)) return rc;
+    if (int rc = check_circuit(h->n, c, max_k)) return rc;
     Plan p;
     if (int rc = plan_fusion(h->n, c->n_gates, c->k, c->targets, c->ctrl_mask, max_k, p, far_qubit(h->amp_bytes())))
         return rc;
@@ -505,9 +544,8 @@ int qs_compile(qs_handle h, const qs_circuit *c, int max_k, qs_program *out)
     std::vector<double> gm;
     int kmax = 1;
     int64_t out_off = 0;
-    // Programs of up to 13 qubits (two tiles) always run by their blocks: on
-    // such states a run in ranges gives the bits of one whole run.
-    pr->tiled = h->n > 13 && plan_tiles(h->n, h->amp_bytes(), c, pr->tiles) && pr->tiles.cost < blocks_cost(h, c, p);
+    pr->tiled = plan_tiles(h->n, h->amp_bytes(), c, pr->tiles) &&
+                program_by_passes(h->n, pr->tiles, blocks_cost(h->amp_bytes(), c, p));
     int n_composed = pr->n_blocks;
     if (pr->tiled) {
         // gates that the passes leave out are composed behind the blocks
@@ -716,18 +754,13 @@ int qs_apply_circuit(qs_handle h, const qs_circuit *c, int max_k)
 {
     clear_error();
     if (int rc = check_handle(h)) return rc;
-    if (int rc = check_circuit(h, c, max_k)) return rc;
-    // Passes need no composed blocks: their words go through the staging
-    // ring and nothing is allocated. A plan with gates of their own, which
-    // would stage matrices over the words, is compiled.
+    if (int rc = check_circuit(h->n, c, max_k)) return rc;
     TilePlan t;
-    const bool planned = plan_tiles(h->n, h->amp_bytes(), c, t) && t.steps.size() == t.passes.size() &&
-                         !t.steps.empty() && t.words.size() * sizeof(uint64_t) <= h->stage.cap;
-    if (planned) {
+    if (plan_tiles(h->n, h->amp_bytes(), c, t) && staged_by_passes(t)) {
         Plan pl;
         if (int rc = plan_fusion(h->n, c->n_gates, c->k, c->targets, c->ctrl_mask, max_k, pl, far_qubit(h->amp_bytes())))
             return rc;
-        if (t.cost < blocks_cost(h, c, pl)) {
+        if (t.cost < blocks_cost(h->amp_bytes(), c, pl)) {
             void *dw = nullptr;
             if (int rc = h->stage.put(h->stream, t.words.data(), t.words.size() * sizeof(uint64_t), &dw)) return rc;
             for (const TilePass &ps : t.passes)

@@ -391,6 +391,7 @@ struct Planner {
             flops += 4.0 * bits(amps) / 16.0 + double(e - i);
             i = e;
         }
+        ++out.ops[kTileDiag];
         w[head] = uint64_t(kTileDiag) | uint64_t(tab) << 6 | uint64_t(sign.size() / kTileSigns) << 8 | groups << 20 |
                   uint64_t(w.size() - head) << 32;
         return 1;
@@ -404,8 +405,9 @@ struct Planner {
     }
 
     void emit(std::vector<uint64_t> &w, int kind, int arg, uint32_t amps, std::initializer_list<uint64_t> masks,
-              const double *m, int count) const
+              const double *m, int count)
     {
+        ++out.ops[kind];
         w.push_back(uint64_t(kind) | uint64_t(arg) << 3 | uint64_t(amps) << 8 |
                     uint64_t(1 + masks.size() + size_t(count)) << 32);
         w.insert(w.end(), masks);
@@ -538,6 +540,7 @@ struct Planner {
             out.words[head] |= ops << 32;
         }
         p.n_stages = int(st.size());
+        out.n_stages += p.n_stages;
         TileStep step;
         step.pass = int(out.passes.size());
         out.passes.push_back(p);

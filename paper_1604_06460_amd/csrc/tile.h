@@ -56,6 +56,8 @@ struct TilePlan {
     std::vector<TileStep> steps;
     std::vector<uint64_t> words;
     double cost = 0;               // estimated time, in sweeps over the state
+    int n_stages = 0;
+    int ops[6] = {0};              // operations by TileOp
 };
 
 double dense_cost(size_t amp_bytes, int k);

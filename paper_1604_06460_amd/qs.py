@@ -44,6 +44,11 @@ class Circuit(C.Structure):
                 ("ctrl_mask", _P), ("ctrl_vals", _P)]
 
 
+class PassPlan(C.Structure):
+    _fields_ = [("n_passes", _I), ("n_stages", _I), ("n_alone", _I), ("ops", _I * 6), ("cost", _D),
+                ("block_cost", _D), ("program", _I), ("circuit", _I)]
+
+
 class Perm(C.Structure):
     _fields_ = [("kind", _I), ("work_lo", _I), ("w", _I), ("ctrl_lo", _I), ("c", _I),
                 ("a", _U64), ("N", _U64), ("lo", _I), ("nbits", _I), ("dest", _P)]
@@ -84,6 +89,7 @@ _sig("qs_load_device", [_P, _P])
 _sig("qs_apply_gate", [_P, _I, _P, _P, _U64, _U64])
 _sig("qs_apply_fused", [_P, _I, _P, _P, _P])
 _sig("qs_plan_fusion", [C.POINTER(Circuit), _I, _I, C.POINTER(_I), _P, _P, _P])
+_sig("qs_plan_passes", [C.POINTER(Circuit), _I, _I, _I, C.POINTER(PassPlan)])
 _sig("qs_compile", [_P, C.POINTER(Circuit), _I, C.POINTER(_P)])
 _sig("qs_program_info", [_P, C.POINTER(_I), _P, C.POINTER(_D)])
 _sig("qs_program_block", [_P, _I, _P, _P])
@@ -276,6 +282,14 @@ def plan_fusion(gates, n_qubits, max_k):
     return bog[:pc.n_gates].copy(), blocks
 
 
+def plan_passes(gates, n_qubits, dtype, max_k):
+    """Host-only plan of a gate list as passes (PassPlan), and who takes it."""
+    pc = PackedCircuit(gates)
+    plan = PassPlan()
+    _chk(_L.qs_plan_passes(C.byref(pc.c), n_qubits, dtype, max_k, C.byref(plan)))
+    return plan
+
+
 class Program:
     def __init__(self, handle):
         self._h = handle
@@ -285,7 +299,7 @@ class Program:
         return self._h
 
     def info(self):
-        """(block count, block widths, amplitude reads + writes per run)."""
+        """(block count, block widths, amplitude reads + writes of a run block by block)."""
         nb = _I(0)
         by = _D(0)
         _chk(_L.qs_program_info(self._h, C.byref(nb), None, C.byref(by)))

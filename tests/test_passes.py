@@ -1,0 +1,58 @@
+"""CPU-only checks of the planner of the tile passes (csrc/passes.cpp) through
+qs_plan_passes: what becomes an operation of a pass, what is left alone, what
+the choice between passes and blocks rests on."""
+import numpy as np
+import pytest
+
+# places in PassPlan.ops
+GENERAL, CONTROLLED, MOVE_X, TWO, REAL, DIAGONAL = range(6)
+
+
+@pytest.fixture(scope="module")
+def Q():
+    from paper_1604_06460_amd import qs
+    return qs
+
+
+def _unitary(rng, k):
+    d = 1 << k
+    q, r = np.linalg.qr(rng.standard_normal((d, d)) + 1j * rng.standard_normal((d, d)))
+    return q * (np.diagonal(r) / np.abs(np.diagonal(r)))
+
+
+def test_plan_counts_what_a_run_does(Q, S):
+    """A layered circuit moves the state once per pass, far less often than
+    block by block; no plan is made for states smaller than a tile."""
+    gates = S.random_layer_circuit(17, 8, seed=3)
+    for dtype in (Q.QS_C64, Q.QS_C128):
+        p = Q.plan_passes(gates, 17, dtype, 4)
+        assert 0 < p.n_passes < p.block_cost and p.cost < p.block_cost
+        assert p.n_alone == 0 and p.n_stages >= p.n_passes
+        assert p.ops[REAL] + p.ops[GENERAL] == 17 * 8 and p.ops[DIAGONAL] > 0
+        assert p.program == 1 and p.circuit == 1
+    small = Q.plan_passes(S.random_layer_circuit(9, 8, seed=3), 9, Q.QS_C128, 4)
+    assert (small.n_passes, small.n_stages, small.cost, small.program, small.circuit) == (0, 0, 0.0, 0, 0)
+    assert small.block_cost > 0
+
+
+def test_plan_of_each_gate(Q, S):
+    rng = np.random.default_rng(1)
+    mixed = _unitary(rng, 2)
+    wide = S.Gate((1, 5, 7), _unitary(rng, 3))
+    cases = [(S.g1(S.MAT_X, 5), MOVE_X, 1), (S.mcx((0, 11), 5), MOVE_X, 1), (S.cnot(3, 9), MOVE_X, 1),
+             (S.swap(2, 9), MOVE_X, 3), (S.g1(S.MAT_H, 5), REAL, 1), (S.cz(4, 9), DIAGONAL, 1),
+             (S.Gate((5,), np.array([[0, -1j], [1j, 0]])), GENERAL, 1), (S.Gate((4, 9), mixed), TWO, 1),
+             (S.Gate((4,), _unitary(rng, 1), 8, 8), CONTROLLED, 1)]
+    for g, op, count in cases:
+        p = Q.plan_passes([g], 12, Q.QS_C128, 4)
+        assert p.n_passes == 1 and p.n_alone == 0 and p.ops[op] == count, (g.name, list(p.ops))
+    p = Q.plan_passes([S.g1(S.MAT_H, 5), wide, S.g1(S.MAT_H, 5)], 15, Q.QS_C128, 4)
+    assert (p.n_passes, p.n_alone) == (2, 1)
+    assert p.circuit == p.program
+
+
+def test_plan_rejects_bad_input(Q, S):
+    g = [S.g1(S.MAT_H, 3)]
+    for args in ((g, 3, Q.QS_C128, 4), (g, 0, Q.QS_C128, 4), (g, 35, Q.QS_C128, 4), (g, 5, 2, 4), (g, 5, Q.QS_C64, 7)):
+        with pytest.raises(Q.QSError):
+            Q.plan_passes(*args)
