@@ -88,10 +88,12 @@ bool as_controlled(const double *m, int &ctrl, int &val, double *u)
 }
 
 // A unitary one-qubit gate as a real matrix (all but a rotation) between
-// phases. False where the matrix is further than rounding from one (it may be
-// any matrix). Every entry keeps its own modulus, so that what rounding left
-// of the gate's norms stays as given: over some hundred gates whose norms are
-// off to the same side it would add up.
+// phases. False where an entry is further from one than a few roundings of
+// its own (it may be any matrix, of any scale): of random unitaries, whose
+// entries have rounding errors of the whole matrix's size, 2 in 100. Every
+// entry keeps its own modulus, so that what rounding left of the gate's norms
+// stays as given: over some hundred gates whose norms are off to the same
+// side it would add up.
 bool as_rotation(TGate &g)
 {
     Phase u[4], a[4];
@@ -107,8 +109,8 @@ bool as_rotation(TGate &g)
     // the second column's phase, from both of its entries by their weight
     const Phase b = a[3] / a[2] * (long double)(g.r[3] * g.r[3]) - a[1] / a[0] * (long double)(g.r[1] * g.r[1]);
     g.before = b / std::abs(b);
-    return std::abs(a[0] * g.before * (long double)(g.r[1]) - u[1]) <= 1e-15L &&
-           std::abs(a[2] * g.before * (long double)(g.r[3]) - u[3]) <= 1e-15L;
+    return std::abs(a[0] * g.before * (long double)(g.r[1]) - u[1]) <= 1e-15L * std::abs(u[1]) &&
+           std::abs(a[2] * g.before * (long double)(g.r[3]) - u[3]) <= 1e-15L * std::abs(u[3]);
 }
 
 void read_gate(int k, const int *targets, const double *m, uint64_t cmask, uint64_t cvals, TGate &g)

@@ -1,0 +1,69 @@
+"""Passes over tiles: gates of any matrix, at any scale, on every qubit, and
+what a caller of programs and circuits relies on around them."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# against the oracle, relative to the state's norm. complex128: some hundred
+# operations of a few roundings of 1.1e-16 each, random in sign. complex64: a
+# rounding of 6e-8 per stage of a pass, or sums of 16 products in FP32 (2.4e-7)
+# in each of some 30 blocks, random in sign.
+TOL = {1: 1e-13, 0: 5e-6}
+
+
+@pytest.fixture(scope="module")
+def Q():
+    from paper_1604_06460_amd import qs
+    return qs
+
+
+def _unitary(rng, k):
+    d = 1 << k
+    q, r = np.linalg.qr(rng.standard_normal((d, d)) + 1j * rng.standard_normal((d, d)))
+    return q * (np.diagonal(r) / np.abs(np.diagonal(r)))
+
+
+def _psi(S, n, dtype):
+    return S.normal_state(n, n).astype(np.complex128 if dtype else np.complex64)
+
+
+def _err(got, ref):
+    return np.linalg.norm(got - ref) / np.linalg.norm(ref)
+
+
+def _runs(Q, S, n, dtype, gates):
+    """The state after a one-call circuit and after a compiled program."""
+    for compiled in (False, True):
+        st = Q.State(n, dtype)
+        st.set(_psi(S, n, dtype))
+        if compiled:
+            prog = st.compile(gates, 4)
+            st.run(prog)
+            prog.free()
+        else:
+            st.apply_circuit(gates, 4)
+        yield st.get()
+        st.free()
+
+
+@pytest.mark.parametrize("dtype", [1, 0])
+@pytest.mark.parametrize("n", [10, 15])
+@pytest.mark.parametrize("scale", [1e-16, 1e-8, 1e-4, 1e12])
+def test_matrices_of_any_scale(Q, O, S, dtype, n, scale):
+    """Layers of unitaries around matrices that are none: two of them random
+    with entries near `scale`, and a scaled unitary off by 1e-16."""
+    rng = np.random.default_rng(n)
+
+    def z():
+        return rng.standard_normal((2, 2)) + 1j * rng.standard_normal((2, 2))
+
+    odd = [S.Gate((n - 1,), scale * z()), S.Gate((2,), z() / scale), S.Gate((5,), scale * _unitary(rng, 1) + 1e-16 * z()),
+           S.Gate((7,), z() / scale)]
+    gates = []
+    for g in odd:
+        gates += S.random_layer_circuit(n, 2, seed=n) + [g]
+    gates += S.random_layer_circuit(n, 2, seed=n + 1)
+    ref = O.apply_circuit(_psi(S, n, dtype).astype(np.complex128), gates)
+    for got in _runs(Q, S, n, dtype, gates):
+        assert _err(got, ref) < TOL[dtype]

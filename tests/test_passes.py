@@ -56,3 +56,29 @@ def test_plan_rejects_bad_input(Q, S):
     for args in ((g, 3, Q.QS_C128, 4), (g, 0, Q.QS_C128, 4), (g, 35, Q.QS_C128, 4), (g, 5, 2, 4), (g, 5, Q.QS_C64, 7)):
         with pytest.raises(Q.QSError):
             Q.plan_passes(*args)
+
+
+@pytest.mark.parametrize("scale", [1e-200, 1e-16, 1e-15, 1e-8, 1.0, 1e8, 1e200])
+def test_matrices_that_are_no_rotation_stay_general(Q, S, scale):
+    """Any 2 x 2 matrix is a gate; only one that is a real matrix between
+    phases, to rounding of each of its entries, may be replaced by these."""
+    rng = np.random.default_rng(4)
+    z = scale * (rng.standard_normal((40, 2, 2)) + 1j * rng.standard_normal((40, 2, 2)))
+    z[0] = scale * np.array([[1, 1e-10 * np.exp(0.3j)], [3e-10, 1]])     # weak: each entry counts
+    p = Q.plan_passes([S.Gate((q % 12,), m) for q, m in enumerate(z)], 12, Q.QS_C128, 4)
+    assert (p.ops[GENERAL], p.ops[REAL]) == (40, 0)
+
+
+def test_scaled_unitaries_are_planned_alike(Q, S):
+    rng = np.random.default_rng(5)
+    us = [_unitary(rng, 1) for _ in range(60)] + [S.MAT_H]
+
+    def ops(scale):
+        return list(Q.plan_passes([S.Gate((q % 12,), scale * u) for q, u in enumerate(us)], 12, Q.QS_C128, 4).ops)
+
+    assert ops(1.0)[REAL] > 50
+    assert ops(2.0 ** -40) == ops(1.0) == ops(2.0 ** 40)
+    # entries that are off by 1e-16 are rounding next to one, not next to 1e-8
+    off = [1e-8 * u + 1e-16 * (rng.standard_normal((2, 2)) + 1j * rng.standard_normal((2, 2))) for u in us]
+    p = Q.plan_passes([S.Gate((q % 12,), m) for q, m in enumerate(off)], 12, Q.QS_C128, 4)
+    assert p.ops[REAL] == 0
