@@ -67,3 +67,20 @@ def test_matrices_of_any_scale(Q, O, S, dtype, n, scale):
     ref = O.apply_circuit(_psi(S, n, dtype).astype(np.complex128), gates)
     for got in _runs(Q, S, n, dtype, gates):
         assert _err(got, ref) < TOL[dtype]
+
+
+def test_long_circuits(Q, O, S):
+    """Some thousand gates: scans that end early, and more phases on qubits
+    that see nothing else than a plan lets wait."""
+    n = 13
+    rng = np.random.default_rng(3)
+    layers = [g for g in S.random_layer_circuit(n, 300, seed=4) if 12 not in g.targets]
+    idle = [S.Gate((11, 12), np.diag(np.exp(2j * np.pi * rng.random(4)))) for _ in range(1500)]
+    mixed = []
+    for i, g in enumerate([g for g in layers if 11 not in g.targets]):
+        mixed += [g] + idle[i % 1500:i % 1500 + 1]
+    for gates in (layers, mixed):
+        # a rounding or two of each gate, at worst all to one side
+        ref = O.apply_circuit(_psi(S, n, 1), gates)
+        for got in _runs(Q, S, n, 1, gates):
+            assert _err(got, ref) < 2 * len(gates) * 2.0 ** -53

@@ -82,3 +82,47 @@ def test_scaled_unitaries_are_planned_alike(Q, S):
     off = [1e-8 * u + 1e-16 * (rng.standard_normal((2, 2)) + 1j * rng.standard_normal((2, 2))) for u in us]
     p = Q.plan_passes([S.Gate((q % 12,), m) for q, m in enumerate(off)], 12, Q.QS_C128, 4)
     assert p.ops[REAL] == 0
+
+
+def _layers(S, rng, n, qubits, count):
+    gates = []
+    while len(gates) < count:
+        gates += S.random_layer_on(qubits, rng)
+    return gates[:count]
+
+
+def _long_circuit(S, name, count):
+    rng = np.random.default_rng(8)
+    if name == "layers":
+        return 25, _layers(S, rng, 25, list(range(25)), count)
+    if name == "idle qubits":                # some idle, one only under phases
+        gates = _layers(S, rng, 25, list(range(20)), count)
+        return 25, [S.cz(g.targets[0], 22) if i % 11 == 0 else g for i, g in enumerate(gates)]
+    if name == "one tile":
+        return 12, _layers(S, rng, 12, list(range(12)), count)
+    if name == "four qubits":
+        return 14, _layers(S, rng, 14, [3, 6, 9, 11], count)
+    if name == "phases":
+        return 25, [S.cr(int(a), int(b), 0.1) for a, b in (rng.permutation(25)[:2] for _ in range(count))]
+    assert name == "alone"
+    wide = S.Gate((1, 5, 7), _unitary(rng, 3))
+    return 16, [wide if i % 2 else S.g1(S.MAT_H, i % 16) for i in range(count)]
+
+
+@pytest.mark.parametrize("name", ["layers", "idle qubits", "one tile", "four qubits", "phases", "alone"])
+def test_planning_time_grows_with_the_gates(Q, S, name):
+    """Eight times the gates take eight times the planning, give or take; a
+    planner that looks at the whole circuit for each pass takes 64 times."""
+    import ctypes
+    import time
+    times = []
+    for count in (5000, 40000):
+        n, gates = _long_circuit(S, name, count)
+        pc, plan, best = Q.PackedCircuit(gates), Q.PassPlan(), float("inf")
+        for _ in range(3):
+            t0 = time.process_time()
+            assert Q.lib().qs_plan_passes(ctypes.byref(pc.c), n, Q.QS_C128, 4, ctypes.byref(plan)) == Q.QS_OK
+            best = min(best, time.process_time() - t0)
+        times.append(best)
+    print("%s: %.1f ms, %.1f ms" % (name, times[0] * 1e3, times[1] * 1e3))
+    assert times[1] < 20 * times[0]
