@@ -274,7 +274,27 @@ constexpr size_t kStageBytes = size_t(8) << 20;
 
 // Programs of up to 13 qubits (two tiles) always run by their blocks: on
 // such states a run in ranges gives the bits of one whole run.
-bool program_by_passes(int n, const TilePlan &t, double block_cost) { return n > 13 && t.cost < block_cost; }
+bool program_by_passes(int n) { return n > 13; }
+
+// A circuit planned both ways; each plan is made once per call. tiled: passes
+// are estimated to be faster than the blocks.
+struct Route {
+    Plan blocks;
+    double block_cost = 0;
+    bool tiled = false;
+    TilePlan tiles;
+};
+
+// once: for qs_apply_circuit
+int plan_route(int n, size_t amp_bytes, const qs_circuit *c, int max_k, bool once, Route &r)
+{
+    if (int rc = plan_fusion(n, c->n_gates, c->k, c->targets, c->ctrl_mask, max_k, r.blocks, far_qubit(amp_bytes)))
+        return rc;
+    r.block_cost = blocks_cost(amp_bytes, c, r.blocks);
+    const bool program = program_by_passes(n);
+    r.tiled = (once || program) && plan_tiles(n, amp_bytes, c, program, r.block_cost, r.tiles);
+    return QS_OK;
+}
 
 // A circuit that runs once: passes need no composed blocks, their words go
 // through the staging ring and nothing is allocated. A plan with gates of
@@ -282,6 +302,153 @@ bool program_by_passes(int n, const TilePlan &t, double block_cost) { return n >
 bool staged_by_passes(const TilePlan &t)
 {
     return t.steps.size() == t.passes.size() && !t.steps.empty() && t.words.size() * sizeof(uint64_t) <= kStageBytes;
+}
+
+// The program of a planned circuit.
+int compile(qs_state *h, const qs_circuit *c, Route &r, qs_program *out)
+{
+    Plan &p = r.blocks;
+    qs_program_t *pr = new (std::nothrow) qs_program_t();
+    if (!pr) return fail(QS_ENOMEM, "host allocation failed");
+    pr->n = h->n;
+    pr->device = h->device;
+    pr->n_blocks = int(p.block_gates.size());
+    // host-side descriptors
+    std::vector<size_t> toff(size_t(c->n_gates) + 1, 0), moff(size_t(c->n_gates) + 1, 0);
+    for (int g = 0; g < c->n_gates; ++g) {
+        toff[size_t(g) + 1] = toff[size_t(g)] + size_t(c->k[g]);
+        moff[size_t(g) + 1] = moff[size_t(g)] + (size_t(2) << (2 * c->k[g]));
+    }
+    std::vector<ComposeGate> cg;
+    std::vector<ComposeBlock> cb;
+    std::vector<double> gm;
+    int kmax = 1;
+    int64_t out_off = 0;
+    pr->tiled = r.tiled && program_by_passes(h->n);
+    int n_composed = pr->n_blocks;
+    if (pr->tiled) {
+        pr->tiles = std::move(r.tiles);
+        // gates that the passes leave out are composed behind the blocks
+        pr->alone.assign(pr->tiles.steps.size(), -1);
+        for (size_t i = 0; i < pr->tiles.steps.size(); ++i) {
+            const int g = pr->tiles.steps[i].gate;
+            if (g < 0) continue;
+            std::vector<int> q(c->targets + toff[size_t(g)], c->targets + toff[size_t(g) + 1]);
+            const uint64_t cm = c->ctrl_mask ? c->ctrl_mask[g] : 0;
+            for (int b = 0; b < 64; ++b)
+                if ((cm >> b) & 1) q.push_back(b);
+            std::sort(q.begin(), q.end());
+            p.block_gates.push_back({g});
+            p.block_qubits.push_back(q);
+            pr->alone[i] = n_composed++;
+        }
+    }
+    for (int b = 0; b < n_composed; ++b) {
+        const auto &qs = p.block_qubits[size_t(b)];
+        const int kb = int(qs.size());
+        kmax = std::max(kmax, kb);
+        auto local = [&](int q) { return int(std::lower_bound(qs.begin(), qs.end(), q) - qs.begin()); };
+        ComposeBlock B;
+        B.k = kb;
+        B.g0 = int(cg.size());
+        bool diag = true;
+        for (int g : p.block_gates[size_t(b)]) {
+            ComposeGate G;
+            std::memset(&G, 0, sizeof G);
+            G.k = c->k[g];
+            for (int m = 0; m < G.k; ++m) G.local_t[m] = local(c->targets[toff[size_t(g)] + size_t(m)]);
+            const uint64_t cm = c->ctrl_mask ? c->ctrl_mask[g] : 0;
+            const uint64_t cv = c->ctrl_vals ? c->ctrl_vals[g] : 0;
+            for (int q = 0; q < 64; ++q)
+                if ((cm >> q) & 1) {
+                    G.ctrl_mask |= 1u << local(q);
+                    if ((cv >> q) & 1) G.ctrl_vals |= 1u << local(q);
+                }
+            G.mat_off = int64_t(gm.size());
+            const double *src = c->matrices + moff[size_t(g)];
+            const size_t cnt = size_t(2) << (2 * G.k);
+            gm.insert(gm.end(), src, src + cnt);
+            GateDesc tmp;
+            classify(src, G.k, tmp);
+            if (!(tmp.cls == GC_IDENTITY || tmp.cls == GC_PHASE1 || tmp.cls == GC_DIAG)) diag = false;
+            cg.push_back(G);
+        }
+        B.g1 = int(cg.size());
+        B.pad = 0;
+        B.out_off = out_off;
+        cb.push_back(B);
+        pr->k.push_back(kb);
+        pr->qubits.push_back(qs);
+        pr->diagonal.push_back(diag ? 1 : 0);
+        pr->mat_off.push_back(out_off);
+        out_off += int64_t(2) << (2 * kb);
+    }
+    pr->mats_doubles = size_t(out_off);
+    int rc = QS_OK;
+    void *dcg = nullptr, *dcb = nullptr, *dgm = nullptr;
+    auto cleanup = [&]() {
+        if (dcg) (void)hipFree(dcg);
+        if (dcb) (void)hipFree(dcb);
+        if (dgm) (void)hipFree(dgm);
+    };
+    auto bail = [&](int r) {
+        cleanup();
+        if (pr->dmats) (void)hipFree(pr->dmats);
+        if (pr->dmats32) (void)hipFree(pr->dmats32);
+        if (pr->dwords) (void)hipFree(pr->dwords);
+        delete pr;
+        return r;
+    };
+    if (pr->tiled) {
+        const size_t bytes = pr->tiles.words.size() * sizeof(uint64_t);
+        hipError_t e = hipMalloc(reinterpret_cast<void **>(&pr->dwords), bytes);
+        if (e == hipSuccess) e = hipMemcpy(pr->dwords, pr->tiles.words.data(), bytes, hipMemcpyHostToDevice);
+        if (e != hipSuccess) return bail(hip_fail(e, "program words"));
+        pr->tiles.words = {};
+    }
+    if (n_composed > 0) {
+        hipError_t e = hipSuccess;
+        if ((e = hipMalloc(&dcg, sizeof(ComposeGate) * cg.size())) != hipSuccess ||
+            (e = hipMalloc(&dcb, sizeof(ComposeBlock) * cb.size())) != hipSuccess ||
+            (e = hipMalloc(&dgm, sizeof(double) * std::max<size_t>(gm.size(), 1))) != hipSuccess ||
+            (e = hipMalloc(reinterpret_cast<void **>(&pr->dmats), sizeof(double) * pr->mats_doubles)) != hipSuccess ||
+            (e = hipMalloc(reinterpret_cast<void **>(&pr->dmats32), sizeof(float) * pr->mats_doubles)) != hipSuccess)
+            return bail(hip_fail(e, "hipMalloc(program)"));
+        if ((e = hipMemcpyAsync(dcg, cg.data(), sizeof(ComposeGate) * cg.size(), hipMemcpyHostToDevice, h->stream)) != hipSuccess ||
+            (e = hipMemcpyAsync(dcb, cb.data(), sizeof(ComposeBlock) * cb.size(), hipMemcpyHostToDevice, h->stream)) != hipSuccess ||
+            (e = hipMemcpyAsync(dgm, gm.data(), sizeof(double) * gm.size(), hipMemcpyHostToDevice, h->stream)) != hipSuccess)
+            return bail(hip_fail(e, "hipMemcpyAsync(program)"));
+        if ((rc = launch_compose(h->stream, n_composed, static_cast<ComposeBlock *>(dcb),
+                                 static_cast<ComposeGate *>(dcg), static_cast<double *>(dgm),
+                                 pr->dmats, kmax)))
+            return bail(rc);
+        if ((rc = launch_cast_f64_to_f32(h->stream, pr->dmats, pr->dmats32, pr->mats_doubles)))
+            return bail(rc);
+        if ((e = hipStreamSynchronize(h->stream)) != hipSuccess)
+            return bail(hip_fail(e, "compose"));
+    }
+    // Diagonal blocks keep their composed diagonal on the host: the run
+    // sweeps only the amplitudes whose entry is not one.
+    pr->hdiag.resize(size_t(pr->n_blocks));
+    pr->changed.assign(size_t(pr->n_blocks), 1.0);
+    for (int b = 0; b < pr->n_blocks; ++b) {
+        if (!pr->diagonal[size_t(b)]) continue;
+        const size_t D = size_t(1) << pr->k[size_t(b)];
+        std::vector<double> full(2 * D * D);
+        hipError_t e = hipMemcpy(full.data(), pr->dmats + pr->mat_off[size_t(b)], full.size() * sizeof(double),
+                                 hipMemcpyDeviceToHost);
+        if (e != hipSuccess) return bail(hip_fail(e, "hipMemcpy(diagonal block)"));
+        auto &hd = pr->hdiag[size_t(b)];
+        hd.resize(2 * D);
+        for (size_t j = 0; j < D; ++j) {
+            hd[2 * j] = full[2 * (j * D + j)];
+            hd[2 * j + 1] = full[2 * (j * D + j) + 1];
+        }
+        pr->changed[size_t(b)] = diag_changed_fraction(hd.data(), pr->k[size_t(b)]);
+    }
+    cleanup();
+    *out = pr;
+    return QS_OK;
 }
 
 }  // namespace
@@ -507,14 +674,15 @@ int qs_plan_passes(const qs_circuit *c, int n_qubits, int dtype, int max_k, qs_p
     *out = qs_pass_plan();
     out->block_cost = blocks_cost(amp, c, p);
     TilePlan t;
-    if (!plan_tiles(n_qubits, amp, c, t)) return QS_OK;
+    if (!plan_tiles(n_qubits, amp, c, true, INFINITY, t)) return QS_OK;
     out->n_passes = int(t.passes.size());
     out->n_stages = t.n_stages;
     out->n_alone = int(t.steps.size() - t.passes.size());
     std::copy_n(t.ops, 6, out->ops);
     out->cost = t.cost;
-    out->program = program_by_passes(n_qubits, t, out->block_cost);
-    out->circuit = staged_by_passes(t) ? t.cost < out->block_cost : out->program;
+    const bool tiled = t.cost < out->block_cost;
+    out->program = tiled && program_by_passes(n_qubits);
+    out->circuit = tiled && (staged_by_passes(t) || out->program);
     return QS_OK;
 }
 
@@ -525,152 +693,9 @@ int qs_compile(qs_handle h, const qs_circuit *c, int max_k, qs_program *out)
     if (!out) return fail(QS_EINVAL, "NULL output program");
     *out = nullptr;
     if (int rc = check_circuit(h->n, c, max_k)) return rc;
-    Plan p;
-    if (int rc = plan_fusion(h->n, c->n_gates, c->k, c->targets, c->ctrl_mask, max_k, p, far_qubit(h->amp_bytes())))
-        return rc;
-    qs_program_t *pr = new (std::nothrow) qs_program_t();
-    if (!pr) return fail(QS_ENOMEM, "host allocation failed");
-    pr->n = h->n;
-    pr->device = h->device;
-    pr->n_blocks = int(p.block_gates.size());
-    // host-side descriptors
-    std::vector<size_t> toff(size_t(c->n_gates) + 1, 0), moff(size_t(c->n_gates) + 1, 0);
-    for (int g = 0; g < c->n_gates; ++g) {
-        toff[size_t(g) + 1] = toff[size_t(g)] + size_t(c->k[g]);
-        moff[size_t(g) + 1] = moff[size_t(g)] + (size_t(2) << (2 * c->k[g]));
-    }
-    std::vector<ComposeGate> cg;
-    std::vector<ComposeBlock> cb;
-    std::vector<double> gm;
-    int kmax = 1;
-    int64_t out_off = 0;
-    pr->tiled = plan_tiles(h->n, h->amp_bytes(), c, pr->tiles) &&
-                program_by_passes(h->n, pr->tiles, blocks_cost(h->amp_bytes(), c, p));
-    int n_composed = pr->n_blocks;
-    if (pr->tiled) {
-        // gates that the passes leave out are composed behind the blocks
-        pr->alone.assign(pr->tiles.steps.size(), -1);
-        for (size_t i = 0; i < pr->tiles.steps.size(); ++i) {
-            const int g = pr->tiles.steps[i].gate;
-            if (g < 0) continue;
-            std::vector<int> q(c->targets + toff[size_t(g)], c->targets + toff[size_t(g) + 1]);
-            const uint64_t cm = c->ctrl_mask ? c->ctrl_mask[g] : 0;
-            for (int b = 0; b < 64; ++b)
-                if ((cm >> b) & 1) q.push_back(b);
-            std::sort(q.begin(), q.end());
-            p.block_gates.push_back({g});
-            p.block_qubits.push_back(q);
-            pr->alone[i] = n_composed++;
-        }
-    } else {
-        pr->tiles = TilePlan();
-    }
-    for (int b = 0; b < n_composed; ++b) {
-        const auto &qs = p.block_qubits[size_t(b)];
-        const int kb = int(qs.size());
-        kmax = std::max(kmax, kb);
-        auto local = [&](int q) { return int(std::lower_bound(qs.begin(), qs.end(), q) - qs.begin()); };
-        ComposeBlock B;
-        B.k = kb;
-        B.g0 = int(cg.size());
-        bool diag = true;
-        for (int g : p.block_gates[size_t(b)]) {
-            ComposeGate G;
-            std::memset(&G, 0, sizeof G);
-            G.k = c->k[g];
-            for (int m = 0; m < G.k; ++m) G.local_t[m] = local(c->targets[toff[size_t(g)] + size_t(m)]);
-            const uint64_t cm = c->ctrl_mask ? c->ctrl_mask[g] : 0;
-            const uint64_t cv = c->ctrl_vals ? c->ctrl_vals[g] : 0;
-            for (int q = 0; q < 64; ++q)
-                if ((cm >> q) & 1) {
-                    G.ctrl_mask |= 1u << local(q);
-                    if ((cv >> q) & 1) G.ctrl_vals |= 1u << local(q);
-                }
-            G.mat_off = int64_t(gm.size());
-            const double *src = c->matrices + moff[size_t(g)];
-            const size_t cnt = size_t(2) << (2 * G.k);
-            gm.insert(gm.end(), src, src + cnt);
-            GateDesc tmp;
-            classify(src, G.k, tmp);
-            if (!(tmp.cls == GC_IDENTITY || tmp.cls == GC_PHASE1 || tmp.cls == GC_DIAG)) diag = false;
-            cg.push_back(G);
-        }
-        B.g1 = int(cg.size());
-        B.pad = 0;
-        B.out_off = out_off;
-        cb.push_back(B);
-        pr->k.push_back(kb);
-        pr->qubits.push_back(qs);
-        pr->diagonal.push_back(diag ? 1 : 0);
-        pr->mat_off.push_back(out_off);
-        out_off += int64_t(2) << (2 * kb);
-    }
-    pr->mats_doubles = size_t(out_off);
-    int rc = QS_OK;
-    void *dcg = nullptr, *dcb = nullptr, *dgm = nullptr;
-    auto cleanup = [&]() {
-        if (dcg) (void)hipFree(dcg);
-        if (dcb) (void)hipFree(dcb);
-        if (dgm) (void)hipFree(dgm);
-    };
-    auto bail = [&](int r) {
-        cleanup();
-        if (pr->dmats) (void)hipFree(pr->dmats);
-        if (pr->dmats32) (void)hipFree(pr->dmats32);
-        if (pr->dwords) (void)hipFree(pr->dwords);
-        delete pr;
-        return r;
-    };
-    if (pr->tiled) {
-        const size_t bytes = pr->tiles.words.size() * sizeof(uint64_t);
-        hipError_t e = hipMalloc(reinterpret_cast<void **>(&pr->dwords), bytes);
-        if (e == hipSuccess) e = hipMemcpy(pr->dwords, pr->tiles.words.data(), bytes, hipMemcpyHostToDevice);
-        if (e != hipSuccess) return bail(hip_fail(e, "program words"));
-        pr->tiles.words = {};
-    }
-    if (n_composed > 0) {
-        hipError_t e = hipSuccess;
-        if ((e = hipMalloc(&dcg, sizeof(ComposeGate) * cg.size())) != hipSuccess ||
-            (e = hipMalloc(&dcb, sizeof(ComposeBlock) * cb.size())) != hipSuccess ||
-            (e = hipMalloc(&dgm, sizeof(double) * std::max<size_t>(gm.size(), 1))) != hipSuccess ||
-            (e = hipMalloc(reinterpret_cast<void **>(&pr->dmats), sizeof(double) * pr->mats_doubles)) != hipSuccess ||
-            (e = hipMalloc(reinterpret_cast<void **>(&pr->dmats32), sizeof(float) * pr->mats_doubles)) != hipSuccess)
-            return bail(hip_fail(e, "hipMalloc(program)"));
-        if ((e = hipMemcpyAsync(dcg, cg.data(), sizeof(ComposeGate) * cg.size(), hipMemcpyHostToDevice, h->stream)) != hipSuccess ||
-            (e = hipMemcpyAsync(dcb, cb.data(), sizeof(ComposeBlock) * cb.size(), hipMemcpyHostToDevice, h->stream)) != hipSuccess ||
-            (e = hipMemcpyAsync(dgm, gm.data(), sizeof(double) * gm.size(), hipMemcpyHostToDevice, h->stream)) != hipSuccess)
-            return bail(hip_fail(e, "hipMemcpyAsync(program)"));
-        if ((rc = launch_compose(h->stream, n_composed, static_cast<ComposeBlock *>(dcb),
-                                 static_cast<ComposeGate *>(dcg), static_cast<double *>(dgm),
-                                 pr->dmats, kmax)))
-            return bail(rc);
-        if ((rc = launch_cast_f64_to_f32(h->stream, pr->dmats, pr->dmats32, pr->mats_doubles)))
-            return bail(rc);
-        if ((e = hipStreamSynchronize(h->stream)) != hipSuccess)
-            return bail(hip_fail(e, "compose"));
-    }
-    // Diagonal blocks keep their composed diagonal on the host: the run
-    // sweeps only the amplitudes whose entry is not one.
-    pr->hdiag.resize(size_t(pr->n_blocks));
-    pr->changed.assign(size_t(pr->n_blocks), 1.0);
-    for (int b = 0; b < pr->n_blocks; ++b) {
-        if (!pr->diagonal[size_t(b)]) continue;
-        const size_t D = size_t(1) << pr->k[size_t(b)];
-        std::vector<double> full(2 * D * D);
-        hipError_t e = hipMemcpy(full.data(), pr->dmats + pr->mat_off[size_t(b)], full.size() * sizeof(double),
-                                 hipMemcpyDeviceToHost);
-        if (e != hipSuccess) return bail(hip_fail(e, "hipMemcpy(diagonal block)"));
-        auto &hd = pr->hdiag[size_t(b)];
-        hd.resize(2 * D);
-        for (size_t j = 0; j < D; ++j) {
-            hd[2 * j] = full[2 * (j * D + j)];
-            hd[2 * j + 1] = full[2 * (j * D + j) + 1];
-        }
-        pr->changed[size_t(b)] = diag_changed_fraction(hd.data(), pr->k[size_t(b)]);
-    }
-    cleanup();
-    *out = pr;
-    return QS_OK;
+    Route r;
+    if (int rc = plan_route(h->n, h->amp_bytes(), c, max_k, false, r)) return rc;
+    return compile(h, c, r, out);
 }
 
 int qs_program_info(qs_program p, int *n_blocks, int *block_k, double *amp_moves_per_run)
@@ -755,21 +780,18 @@ int qs_apply_circuit(qs_handle h, const qs_circuit *c, int max_k)
     clear_error();
     if (int rc = check_handle(h)) return rc;
     if (int rc = check_circuit(h->n, c, max_k)) return rc;
-    TilePlan t;
-    if (plan_tiles(h->n, h->amp_bytes(), c, t) && staged_by_passes(t)) {
-        Plan pl;
-        if (int rc = plan_fusion(h->n, c->n_gates, c->k, c->targets, c->ctrl_mask, max_k, pl, far_qubit(h->amp_bytes())))
-            return rc;
-        if (t.cost < blocks_cost(h->amp_bytes(), c, pl)) {
-            void *dw = nullptr;
-            if (int rc = h->stage.put(h->stream, t.words.data(), t.words.size() * sizeof(uint64_t), &dw)) return rc;
-            for (const TilePass &ps : t.passes)
-                if (int rc = launch_tile_pass(h, ps, static_cast<const uint64_t *>(dw))) return rc;
-            return QS_OK;
-        }
+    Route r;
+    if (int rc = plan_route(h->n, h->amp_bytes(), c, max_k, true, r)) return rc;
+    if (r.tiled && staged_by_passes(r.tiles)) {
+        const TilePlan &t = r.tiles;
+        void *dw = nullptr;
+        if (int rc = h->stage.put(h->stream, t.words.data(), t.words.size() * sizeof(uint64_t), &dw)) return rc;
+        for (const TilePass &ps : t.passes)
+            if (int rc = launch_tile_pass(h, ps, static_cast<const uint64_t *>(dw))) return rc;
+        return QS_OK;
     }
     qs_program p = nullptr;
-    if (int rc = qs_compile(h, c, max_k, &p)) return rc;
+    if (int rc = compile(h, c, r, &p)) return rc;
     int rc = qs_run_program(h, p);
     qs_program_free(p);
     return rc;

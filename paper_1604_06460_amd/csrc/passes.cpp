@@ -615,7 +615,7 @@ double dense_cost(size_t amp_bytes, int k)
     return k == 5 ? 1.2 : 1.55;
 }
 
-bool plan_tiles(int n, size_t amp_bytes, const qs_circuit *c, TilePlan &out)
+bool plan_tiles(int n, size_t amp_bytes, const qs_circuit *c, bool alone, double limit, TilePlan &out)
 {
     out = TilePlan();
     if (n < kTileBitsMin) return false;
@@ -633,6 +633,7 @@ bool plan_tiles(int n, size_t amp_bytes, const qs_circuit *c, TilePlan &out)
         read_gate(c->k[g], tp, mp, cm, c->ctrl_vals ? c->ctrl_vals[g] & cm : 0, gates[size_t(g)]);
         tp += c->k[g];
         mp += size_t(2) << (2 * c->k[g]);
+        if (gates[size_t(g)].kind == kAlone && !alone) return false;
         if (gates[size_t(g)].kind != kNothing) left.add(g, gates[size_t(g)]);
     }
     Planner pl(n, T, low, gates, out);
@@ -641,14 +642,23 @@ bool plan_tiles(int n, size_t amp_bytes, const qs_circuit *c, TilePlan &out)
     // of one for each pass, and saves a fifth of the passes: worth it once a
     // pass takes as long.
     const bool search = (amp_bytes << n) >= (size_t(1) << 29);
+    // Estimated time in sweeps: a pass moves the state as a sweep does, with
+    // longer strides, and its multiply-adds hide behind the memory in part
+    // (30 TFMA/s against 6 TB/s); an unfused gate on up to four qubits is a
+    // sweep.
+    const double fma = (30e12 / 6e12) * 2.0 * double(amp_bytes);
+    double swept = 0;
+    auto cost = [&]() { return 1.2 * double(out.passes.size()) + 0.8 * pl.flops / fma + swept; };
     auto front_alone = [&]() { return !left.empty() && gates[size_t(left.ids[left.front])].kind == kAlone; };
     while (!left.empty()) {
         if (front_alone()) {
             TileStep s;
             s.gate = left.ids[left.front++];
             out.steps.push_back(s);
+            swept += dense_cost(amp_bytes, c->k[s.gate]);
             continue;
         }
+        if (cost() >= limit) break;
         uint64_t S = lowmask;
         if (search) S = pl.best_tile(left, S);
         pl.closure(left, S, true);
@@ -657,15 +667,10 @@ bool plan_tiles(int n, size_t amp_bytes, const qs_circuit *c, TilePlan &out)
         pl.pass(S, ex, left.empty() || front_alone());
     }
     out.words.insert(out.words.end(), size_t(kTileAhead), 0);
-    // Estimated time in sweeps: a pass moves the state as a sweep does, with
-    // longer strides, and its multiply-adds hide behind the memory in part
-    // (30 TFMA/s against 6 TB/s); an unfused gate on up to four qubits is a
-    // sweep.
-    const double fma = (30e12 / 6e12) * 2.0 * double(amp_bytes);
-    out.cost = 1.2 * double(out.passes.size()) + 0.8 * pl.flops / fma;
-    for (const TileStep &s : out.steps)
-        if (s.gate >= 0) out.cost += dense_cost(amp_bytes, c->k[s.gate]);
-    return true;
+    out.cost = cost();
+    if (out.cost < limit) return true;
+    out = TilePlan();
+    return false;
 }
 
 }  // namespace qs

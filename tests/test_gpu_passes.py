@@ -1,5 +1,7 @@
 """Passes over tiles: gates of any matrix, at any scale, on every qubit, and
 what a caller of programs and circuits relies on around them."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -84,3 +86,42 @@ def test_long_circuits(Q, O, S):
         ref = O.apply_circuit(_psi(S, n, 1), gates)
         for got in _runs(Q, S, n, 1, gates):
             assert _err(got, ref) < 2 * len(gates) * 2.0 ** -53
+
+
+@pytest.mark.parametrize("n", [12, 15])
+def test_one_call_plans_once(Q, S, n):
+    """A long circuit that stays on blocks: one call takes no longer than
+    compiling, running and freeing a program, which plans it once."""
+    import time
+    rng = np.random.default_rng(6)
+    wide = [S.Gate(tuple(int(x) for x in rng.permutation(n)[:3]), _unitary(rng, 3)) for _ in range(40)]
+    layers = S.random_layer_circuit(n, 1400, seed=2)
+    gates = []
+    for i, g in enumerate(layers):
+        gates += [g] if i % 6 else [g, wide[i % 40]]
+    assert Q.plan_passes(gates, n, Q.QS_C128, 4).circuit == 0
+    st = Q.State(n, Q.QS_C128)
+    pc = Q.PackedCircuit(gates)
+
+    def one_call():
+        assert Q.lib().qs_apply_circuit(st.handle, C.byref(pc.c), 4) == Q.QS_OK
+
+    def three_calls():
+        p = C.c_void_p()
+        assert Q.lib().qs_compile(st.handle, C.byref(pc.c), 4, C.byref(p)) == Q.QS_OK
+        assert Q.lib().qs_run_program(st.handle, p) == Q.QS_OK
+        assert Q.lib().qs_program_free(p) == Q.QS_OK
+
+    best = {}
+    for fn in (one_call, three_calls):
+        fn()
+        st.sync()
+        best[fn] = float("inf")
+        for _ in range(5):
+            t0 = time.perf_counter()
+            fn()
+            st.sync()
+            best[fn] = min(best[fn], time.perf_counter() - t0)
+    print("one call %.2f ms, compile, run and free %.2f ms" % (best[one_call] * 1e3, best[three_calls] * 1e3))
+    assert best[one_call] < 1.1 * best[three_calls]
+    st.free()
