@@ -241,16 +241,18 @@ int qs_program_block_kind(qs_program p, int b, int *kind, double *changed_fracti
  * ascending qubit list (k ints) to the host. */
 int qs_program_block(qs_program p, int b, double *matrix_out, int *qubits_out);
 
-/* Enqueue one run of the program on the handle: block by block, or, where
- * that is estimated to be faster (states of 14 qubits or more), as passes
- * that apply many gates to tiles of the state, in an order that commutes
- * with the blocks'. */
+/* Enqueue one run of the program on the handle: block by block, or, on
+ * states of 14 qubits or more and where that is estimated to be faster, as
+ * passes that apply many gates to tiles of the state, in an order that
+ * commutes with the blocks'. */
 int qs_run_program(qs_handle h, qs_program p);
 
 /* Enqueue blocks [b0, b1) of the program, in order (0 <= b0 <= b1 <=
- * n_blocks, else QS_EINVAL): running consecutive ranges equals one run (bit
- * for bit up to 13 qubits, to rounding above, where one run may use passes).
- * Lets a caller put events between blocks to time each launch. */
+ * n_blocks, else QS_EINVAL), always block by block: running consecutive
+ * ranges gives the bits of running [0, n_blocks) at once. It equals one
+ * qs_run_program to rounding, and bit for bit where that runs block by block
+ * too, as it does up to 13 qubits. Lets a caller put events between blocks to
+ * time each launch. */
 int qs_run_program_range(qs_handle h, qs_program p, int b0, int b1);
 
 int qs_program_free(qs_program p);

@@ -125,3 +125,35 @@ def test_one_call_plans_once(Q, S, n):
     print("one call %.2f ms, compile, run and free %.2f ms" % (best[one_call] * 1e3, best[three_calls] * 1e3))
     assert best[one_call] < 1.1 * best[three_calls]
     st.free()
+
+
+@pytest.mark.parametrize("dtype", [1, 0])
+@pytest.mark.parametrize("k", [4, 6])
+@pytest.mark.parametrize("n", [10, 13, 14, 18])
+def test_ranges_are_the_blocks(Q, O, S, n, k, dtype):
+    """Block ranges give the same bits however they are cut, and one run equals
+    them: to rounding where it takes passes, else bit for bit."""
+    gates = S.random_layer_circuit(n, 5, seed=n + k)
+    ref = O.apply_circuit(_psi(S, n, dtype).astype(np.complex128), gates)
+    plan = Q.plan_passes(gates, n, dtype, k)
+    assert plan.program == (n > 13)
+    st = Q.State(n, dtype)
+    prog = st.compile(gates, k)
+    nb = prog.info()[0]
+    out = []
+    for cuts in ([0, nb], [0, nb // 3, nb // 3, nb], list(range(nb + 1))):
+        st.set(_psi(S, n, dtype))
+        for b0, b1 in zip(cuts[:-1], cuts[1:]):
+            st.run_range(prog, b0, b1)
+        out.append(st.get())
+    for other in out[1:]:
+        assert np.array_equal(out[0].view(np.uint8), other.view(np.uint8))
+    assert _err(out[0], ref) < TOL[dtype]
+    st.set(_psi(S, n, dtype))
+    st.run(prog)
+    run = st.get()
+    assert _err(run, ref) < TOL[dtype]
+    if not plan.program:
+        assert np.array_equal(out[0].view(np.uint8), run.view(np.uint8))
+    prog.free()
+    st.free()
