@@ -257,7 +257,13 @@ int qs_run_program_range(qs_handle h, qs_program p, int b0, int b1);
 
 int qs_program_free(qs_program p);
 
-/* Compile with max_k, run once, free. */
+/* One run of a circuit that is used once: its passes where these are
+ * estimated to be faster and take every gate (nothing is composed or
+ * allocated then), else compiled with max_k, run and freed. Returns once
+ * enqueued, like every gate call: a caller that reads a lent buffer on another
+ * stream waits for the handle's stream first. QS_EUNSUPPORTED while the stream
+ * is being captured (a graph would keep neither the circuit nor the blocks):
+ * capture a run of a compiled program instead. */
 int qs_apply_circuit(qs_handle h, const qs_circuit *c, int max_k);
 
 /* ---------------------------------------------------------------------- */

@@ -783,6 +783,11 @@ int qs_apply_circuit(qs_handle h, const qs_circuit *c, int max_k)
     clear_error();
     if (int rc = check_handle(h)) return rc;
     if (int rc = check_circuit(h->n, c, max_k)) return rc;
+    // a replay would read whatever the staging ring holds by then
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(h->stream, &cap) != hipSuccess) (void)hipGetLastError();
+    if (cap != hipStreamCaptureStatusNone)
+        return fail(QS_EUNSUPPORTED, "qs_apply_circuit on a stream that is being captured: compile the circuit first");
     Route r;
     if (int rc = plan_route(h->n, h->amp_bytes(), c, max_k, true, r)) return rc;
     if (r.tiled && staged_by_passes(r.tiles)) {

@@ -157,3 +157,33 @@ def test_ranges_are_the_blocks(Q, O, S, n, k, dtype):
         assert np.array_equal(out[0].view(np.uint8), run.view(np.uint8))
     prog.free()
     st.free()
+
+
+@pytest.mark.parametrize("dtype", [1, 0])
+def test_capture(Q, S, dtype):
+    """A program's passes replay from a graph with the bits of an eager run;
+    a one-call circuit, whose words a graph would not keep, is refused and
+    leaves the capture as it was."""
+    import torch
+    n = 15
+    gates = S.random_layer_circuit(n, 5, seed=9)
+    stream = torch.cuda.Stream()
+    st = Q.State(n, dtype, stream=stream.cuda_stream)
+    prog = st.compile(gates, 4)
+    assert Q.plan_passes(gates, n, dtype, 4).program == 1
+    st.set(_psi(S, n, dtype))
+    st.run(prog)
+    eager = st.get()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        with pytest.raises(Q.QSError):
+            st.apply_circuit(gates, 4)
+        st.run(prog)
+    for seed in range(3):
+        st.apply_circuit(S.random_layer_circuit(n, 3, seed=seed), 4)     # other work in the ring
+        st.set(_psi(S, n, dtype))
+        with torch.cuda.stream(stream):
+            graph.replay()
+        assert np.array_equal(st.get().view(np.uint8), eager.view(np.uint8))
+    prog.free()
+    st.free()
