@@ -200,7 +200,7 @@ typedef struct qs_pass_plan {
     int ops[6];          /* operations of the passes: general one-qubit, the
                             same under controls, X, two-qubit, real
                             one-qubit, diagonal */
-    double cost;         /* estimated time, in sweeps over the state */
+    double cost;         /* estimated time in microseconds */
     double block_cost;   /* the same for the blocks */
     int program;         /* 1 if qs_run_program takes the passes */
     int circuit;         /* 1 if qs_apply_circuit takes them */

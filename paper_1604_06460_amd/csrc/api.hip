@@ -249,9 +249,8 @@ int check_circuit(int n, const qs_circuit *c, int max_k)
     return QS_OK;
 }
 
-// Estimated time of a plan's blocks, in sweeps. A block of diagonal gates
-// sweeps only what it changes, a quarter of the state for a CZ.
-double blocks_cost(size_t amp_bytes, const qs_circuit *c, const Plan &p)
+// Estimated time of a plan's blocks in microseconds.
+double blocks_cost(int n, size_t amp_bytes, const qs_circuit *c, const Plan &p)
 {
     std::vector<char> diag(size_t(std::max(0, c->n_gates)));
     const double *m = c->matrices;
@@ -265,7 +264,7 @@ double blocks_cost(size_t amp_bytes, const qs_circuit *c, const Plan &p)
     for (size_t b = 0; b < p.block_gates.size(); ++b) {
         bool all = true;
         for (int g : p.block_gates[b]) all = all && diag[size_t(g)];
-        cost += all ? 0.25 : dense_cost(amp_bytes, int(p.block_qubits[b].size()));
+        cost += all ? diagonal_us(n, amp_bytes) : dense_us(n, amp_bytes, int(p.block_qubits[b].size()));
     }
     return cost;
 }
@@ -294,7 +293,7 @@ int plan_route(int n, size_t amp_bytes, const qs_circuit *c, int max_k, bool onc
 {
     if (int rc = plan_fusion(n, c->n_gates, c->k, c->targets, c->ctrl_mask, max_k, r.blocks, far_qubit(amp_bytes)))
         return rc;
-    r.block_cost = blocks_cost(amp_bytes, c, r.blocks);
+    r.block_cost = blocks_cost(n, amp_bytes, c, r.blocks);
     const bool program = program_by_passes(n);
     r.tiled = (once || program) && plan_tiles(n, amp_bytes, c, program, r.block_cost, r.tiles);
     return QS_OK;
@@ -676,7 +675,7 @@ int qs_plan_passes(const qs_circuit *c, int n_qubits, int dtype, int max_k, qs_p
     Plan p;
     if (int rc = plan_fusion(n_qubits, c->n_gates, c->k, c->targets, c->ctrl_mask, max_k, p, far_qubit(amp))) return rc;
     *out = qs_pass_plan();
-    out->block_cost = blocks_cost(amp, c, p);
+    out->block_cost = blocks_cost(n_qubits, amp, c, p);
     TilePlan t;
     if (!plan_tiles(n_qubits, amp, c, true, INFINITY, t)) return QS_OK;
     out->n_passes = int(t.passes.size());

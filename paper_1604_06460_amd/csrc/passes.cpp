@@ -474,9 +474,10 @@ struct Planner {
             return 1;
         }
         if (g.kind == kOne) {
-            flops += g.x ? 2 : 8;
             uint64_t om = 0, ov = 0;
             const uint32_t amps = registers(reg_bit, g.diag, g.cvals, om, ov);
+            // an X moves both words of its values by three logic instructions each
+            flops += 8.0 * bits(amps) / 16.0;
             if (g.x) emit(w, kTileX, a, amps, {om, ov}, nullptr, 0);
             else if (g.diag) emit(w, kTileCDense1, a, amps, {om, ov}, g.m, 8);
             else emit(w, kTileDense1, a, 0, {}, g.m, 8);
@@ -491,7 +492,7 @@ struct Planner {
                 for (int j = 0; j < 16; ++j) amps |= uint32_t((j >> ctl) & 1) << j;
                 emit(w, kTileX, x, amps, {0, 0}, nullptr, 0);
             }
-            flops += 6;
+            flops += 12;
             return 3;
         }
         // local bit 0 = the lower register bit
@@ -605,14 +606,42 @@ struct Planner {
 
 }  // namespace
 
-// Time of a dense sweep of a k-qubit block, in sweeps limited by memory
-// alone (30 qubits, complex128: 5.7 ms for k <= 4, 6.6 and 21.3 ms for k = 5
-// and 6; complex64: 2.9, 3.5 and 4.5 ms).
-double dense_cost(size_t amp_bytes, int k)
+// Estimated times, in microseconds. The choice between passes and blocks
+// rests on them. Both ways were timed on 764 circuits of 10 to 27 qubits in
+// both types and blocks of 2 to 6 (random layers, dense two-qubit gates in
+// pairs and in rows, controlled one-qubit gates, Toffolis, Hadamards with
+// CNOTs, QFTs, Ising steps, adders, mixtures, and gates left alone under one
+// and four controls): the slower way is taken for 13 of them, by 16 % at most.
+
+// Reading and writing the state once at 6 TB/s.
+static double sweep_us(int n, size_t amp_bytes) { return std::ldexp(2.0 * double(amp_bytes), n) / 6e6; }
+
+// One dense block of k qubits. A launch on a state too small to fill the chip
+// takes the first term (fewer than 6 + k qubits leave a 5- or 6-qubit block
+// to a few threads); the second is the sweep's (30 qubits, complex128: 5.7 ms
+// for k <= 4, 6.6 and 21.3 ms for k = 5 and 6; complex64: 2.9, 3.5 and 4.5 ms).
+double dense_us(int n, size_t amp_bytes, int k)
 {
-    if (k <= 4) return 1.0;
-    if (amp_bytes == 16) return k == 5 ? 1.2 : 3.7;
-    return k == 5 ? 1.2 : 1.55;
+    const bool c128 = amp_bytes == 16;
+    const double mem = sweep_us(n, amp_bytes);
+    if (k <= 4) return (k <= 3 ? 4.0 : c128 ? 5.6 : 4.5) + mem;
+    if (k == 5) return (n < 11 ? 22.0 : c128 ? 8.0 : 7.0) + 1.2 * mem;
+    return (n < 12 ? (c128 ? 35.0 : 100.0) : c128 ? 18.0 : 9.0) + (c128 ? 3.7 : 1.55) * mem;
+}
+
+// A block of diagonal gates sweeps only what it changes, a quarter of the
+// state for a CZ.
+double diagonal_us(int n, size_t amp_bytes) { return 4.0 + 0.25 * sweep_us(n, amp_bytes); }
+
+// The passes: per pass, stage and operation what a workgroup takes alone,
+// which is all on a small state, and their memory and arithmetic (flops in
+// multiply-adds per amplitude, 30 T of them a second) on a large one.
+static double passes_us(int n, size_t amp_bytes, const TilePlan &p, double flops)
+{
+    const double mem = sweep_us(n, amp_bytes), fma = (30e12 / 6e12) * 2.0 * double(amp_bytes);
+    const double moves = p.ops[kTileCDense1] + p.ops[kTileX] + p.ops[kTileDense2];
+    return 4.2 * double(p.passes.size()) + 1.2 * p.n_stages + 0.28 * moves + 0.74 * p.ops[kTileDiag] +
+           mem * (0.52 * double(p.passes.size()) + 0.79 * flops / fma);
 }
 
 bool plan_tiles(int n, size_t amp_bytes, const qs_circuit *c, bool alone, double limit, TilePlan &out)
@@ -642,20 +671,16 @@ bool plan_tiles(int n, size_t amp_bytes, const qs_circuit *c, bool alone, double
     // of one for each pass, and saves a fifth of the passes: worth it once a
     // pass takes as long.
     const bool search = (amp_bytes << n) >= (size_t(1) << 29);
-    // Estimated time in sweeps: a pass moves the state as a sweep does, with
-    // longer strides, and its multiply-adds hide behind the memory in part
-    // (30 TFMA/s against 6 TB/s); an unfused gate on up to four qubits is a
-    // sweep.
-    const double fma = (30e12 / 6e12) * 2.0 * double(amp_bytes);
     double swept = 0;
-    auto cost = [&]() { return 1.2 * double(out.passes.size()) + 0.8 * pl.flops / fma + swept; };
+    auto cost = [&]() { return passes_us(n, amp_bytes, out, pl.flops) + swept; };
     auto front_alone = [&]() { return !left.empty() && gates[size_t(left.ids[left.front])].kind == kAlone; };
     while (!left.empty()) {
         if (front_alone()) {
             TileStep s;
             s.gate = left.ids[left.front++];
             out.steps.push_back(s);
-            swept += dense_cost(amp_bytes, c->k[s.gate]);
+            // a block over its targets and controls
+            swept += dense_us(n, amp_bytes, bits(gates[size_t(s.gate)].need | gates[size_t(s.gate)].diag));
             continue;
         }
         if (cost() >= limit) break;

@@ -55,12 +55,14 @@ struct TilePlan {
     std::vector<TilePass> passes;
     std::vector<TileStep> steps;
     std::vector<uint64_t> words;
-    double cost = 0;               // estimated time, in sweeps over the state
+    double cost = 0;               // estimated time in microseconds
     int n_stages = 0;
     int ops[6] = {0};              // operations by TileOp
 };
 
-double dense_cost(size_t amp_bytes, int k);
+// Estimated times of a dense and of a diagonal block, in microseconds.
+double dense_us(int n, size_t amp_bytes, int k);
+double diagonal_us(int n, size_t amp_bytes);
 
 // False where no plan is made: states smaller than a tile, a gate of its own
 // where `alone` does not allow any, or a cost of `limit` or more (planning

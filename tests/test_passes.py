@@ -26,7 +26,7 @@ def test_plan_counts_what_a_run_does(Q, S):
     gates = S.random_layer_circuit(17, 8, seed=3)
     for dtype in (Q.QS_C64, Q.QS_C128):
         p = Q.plan_passes(gates, 17, dtype, 4)
-        assert 0 < p.n_passes < p.block_cost and p.cost < p.block_cost
+        assert 0 < p.n_passes < len(Q.plan_fusion(gates, 17, 4)[1]) and p.cost < p.block_cost
         assert p.n_alone == 0 and p.n_stages >= p.n_passes
         assert p.ops[REAL] + p.ops[GENERAL] == 17 * 8 and p.ops[DIAGONAL] > 0
         assert p.program == 1 and p.circuit == 1
@@ -126,3 +126,30 @@ def test_planning_time_grows_with_the_gates(Q, S, name):
         times.append(best)
     print("%s: %.1f ms, %.1f ms" % (name, times[0] * 1e3, times[1] * 1e3))
     assert times[1] < 20 * times[0]
+
+
+@pytest.mark.parametrize("n", [14, 26])
+def test_gates_alone_are_priced_by_all_their_qubits(Q, S, n):
+    """A gate left alone runs as a block over targets and controls."""
+    rng = np.random.default_rng(2)
+    for dtype in (Q.QS_C64, Q.QS_C128):
+        def cost(gate):
+            return Q.plan_passes([S.g1(S.MAT_H, 5), gate], n, dtype, 4).cost
+
+        controlled = cost(S.Gate((0, 1), _unitary(rng, 2), 0xf00, 0xf00))
+        assert controlled == cost(S.Gate((0, 1, 8, 9, 10, 11), _unitary(rng, 6)))
+        assert controlled > cost(S.Gate((0, 1), _unitary(rng, 2), 0x100, 0x100))
+
+
+def test_price_of_moves(Q, S):
+    """An X costs the kernel as many instructions as a general gate (a real
+    rotation half of them), a SWAP one and a half times that."""
+    n = 30
+    base = Q.plan_passes([S.g1(S.MAT_H, 5)], n, Q.QS_C128, 4).cost
+    y = np.array([[0, -1j], [1j, 0]])
+
+    def extra(gate):
+        return Q.plan_passes([S.g1(S.MAT_H, 5), gate], n, Q.QS_C128, 4).cost - base
+
+    assert extra(S.g1(S.MAT_X, 9)) == pytest.approx(extra(S.Gate((9,), y)), rel=0.01)
+    assert extra(S.swap(9, 11)) == pytest.approx(1.5 * extra(S.Gate((9,), y)), rel=0.01)
