@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <numeric>
 
@@ -307,12 +308,28 @@ bool staged_by_passes(const TilePlan &t)
     return t.steps.size() == t.passes.size() && !t.steps.empty() && t.words.size() * sizeof(uint64_t) <= kStageBytes;
 }
 
+// A device allocation of one call.
+struct DeviceTemp {
+    void *p = nullptr;
+    ~DeviceTemp()
+    {
+        if (p) (void)hipFree(p);
+    }
+};
+
+void free_program(qs_program_t *p)
+{
+    if (p->dwords) (void)hipFree(p->dwords);
+    if (p->dmats) (void)hipFree(p->dmats);
+    if (p->dmats32) (void)hipFree(p->dmats32);
+    delete p;
+}
+
 // The program of a planned circuit.
 int compile(qs_state *h, const qs_circuit *c, Route &r, qs_program *out)
 {
     Plan &p = r.blocks;
-    qs_program_t *pr = new (std::nothrow) qs_program_t();
-    if (!pr) return fail(QS_ENOMEM, "host allocation failed");
+    std::unique_ptr<qs_program_t, void (*)(qs_program_t *)> pr(new qs_program_t(), free_program);
     pr->n = h->n;
     pr->device = h->device;
     pr->n_blocks = int(p.block_gates.size());
@@ -388,47 +405,34 @@ int compile(qs_state *h, const qs_circuit *c, Route &r, qs_program *out)
     }
     pr->mats_doubles = size_t(out_off);
     int rc = QS_OK;
-    void *dcg = nullptr, *dcb = nullptr, *dgm = nullptr;
-    auto cleanup = [&]() {
-        if (dcg) (void)hipFree(dcg);
-        if (dcb) (void)hipFree(dcb);
-        if (dgm) (void)hipFree(dgm);
-    };
-    auto bail = [&](int r) {
-        cleanup();
-        if (pr->dmats) (void)hipFree(pr->dmats);
-        if (pr->dmats32) (void)hipFree(pr->dmats32);
-        if (pr->dwords) (void)hipFree(pr->dwords);
-        delete pr;
-        return r;
-    };
+    DeviceTemp dcg, dcb, dgm;
     if (pr->tiled) {
         const size_t bytes = pr->tiles.words.size() * sizeof(uint64_t);
         hipError_t e = hipMalloc(reinterpret_cast<void **>(&pr->dwords), bytes);
         if (e == hipSuccess) e = hipMemcpy(pr->dwords, pr->tiles.words.data(), bytes, hipMemcpyHostToDevice);
-        if (e != hipSuccess) return bail(hip_fail(e, "program words"));
+        if (e != hipSuccess) return hip_fail(e, "program words");
         pr->tiles.words = {};
     }
     if (n_composed > 0) {
         hipError_t e = hipSuccess;
-        if ((e = hipMalloc(&dcg, sizeof(ComposeGate) * cg.size())) != hipSuccess ||
-            (e = hipMalloc(&dcb, sizeof(ComposeBlock) * cb.size())) != hipSuccess ||
-            (e = hipMalloc(&dgm, sizeof(double) * std::max<size_t>(gm.size(), 1))) != hipSuccess ||
+        if ((e = hipMalloc(&dcg.p, sizeof(ComposeGate) * cg.size())) != hipSuccess ||
+            (e = hipMalloc(&dcb.p, sizeof(ComposeBlock) * cb.size())) != hipSuccess ||
+            (e = hipMalloc(&dgm.p, sizeof(double) * std::max<size_t>(gm.size(), 1))) != hipSuccess ||
             (e = hipMalloc(reinterpret_cast<void **>(&pr->dmats), sizeof(double) * pr->mats_doubles)) != hipSuccess ||
             (e = hipMalloc(reinterpret_cast<void **>(&pr->dmats32), sizeof(float) * pr->mats_doubles)) != hipSuccess)
-            return bail(hip_fail(e, "hipMalloc(program)"));
-        if ((e = hipMemcpyAsync(dcg, cg.data(), sizeof(ComposeGate) * cg.size(), hipMemcpyHostToDevice, h->stream)) != hipSuccess ||
-            (e = hipMemcpyAsync(dcb, cb.data(), sizeof(ComposeBlock) * cb.size(), hipMemcpyHostToDevice, h->stream)) != hipSuccess ||
-            (e = hipMemcpyAsync(dgm, gm.data(), sizeof(double) * gm.size(), hipMemcpyHostToDevice, h->stream)) != hipSuccess)
-            return bail(hip_fail(e, "hipMemcpyAsync(program)"));
-        if ((rc = launch_compose(h->stream, n_composed, static_cast<ComposeBlock *>(dcb),
-                                 static_cast<ComposeGate *>(dcg), static_cast<double *>(dgm),
+            return hip_fail(e, "hipMalloc(program)");
+        if ((e = hipMemcpyAsync(dcg.p, cg.data(), sizeof(ComposeGate) * cg.size(), hipMemcpyHostToDevice, h->stream)) != hipSuccess ||
+            (e = hipMemcpyAsync(dcb.p, cb.data(), sizeof(ComposeBlock) * cb.size(), hipMemcpyHostToDevice, h->stream)) != hipSuccess ||
+            (e = hipMemcpyAsync(dgm.p, gm.data(), sizeof(double) * gm.size(), hipMemcpyHostToDevice, h->stream)) != hipSuccess)
+            return hip_fail(e, "hipMemcpyAsync(program)");
+        if ((rc = launch_compose(h->stream, n_composed, static_cast<ComposeBlock *>(dcb.p),
+                                 static_cast<ComposeGate *>(dcg.p), static_cast<double *>(dgm.p),
                                  pr->dmats, kmax)))
-            return bail(rc);
+            return rc;
         if ((rc = launch_cast_f64_to_f32(h->stream, pr->dmats, pr->dmats32, pr->mats_doubles)))
-            return bail(rc);
+            return rc;
         if ((e = hipStreamSynchronize(h->stream)) != hipSuccess)
-            return bail(hip_fail(e, "compose"));
+            return hip_fail(e, "compose");
     }
     // Diagonal blocks keep their composed diagonal on the host: the run
     // sweeps only the amplitudes whose entry is not one.
@@ -440,7 +444,7 @@ int compile(qs_state *h, const qs_circuit *c, Route &r, qs_program *out)
         std::vector<double> full(2 * D * D);
         hipError_t e = hipMemcpy(full.data(), pr->dmats + pr->mat_off[size_t(b)], full.size() * sizeof(double),
                                  hipMemcpyDeviceToHost);
-        if (e != hipSuccess) return bail(hip_fail(e, "hipMemcpy(diagonal block)"));
+        if (e != hipSuccess) return hip_fail(e, "hipMemcpy(diagonal block)");
         auto &hd = pr->hdiag[size_t(b)];
         hd.resize(2 * D);
         for (size_t j = 0; j < D; ++j) {
@@ -449,8 +453,7 @@ int compile(qs_state *h, const qs_circuit *c, Route &r, qs_program *out)
         }
         pr->changed[size_t(b)] = diag_changed_fraction(hd.data(), pr->k[size_t(b)]);
     }
-    cleanup();
-    *out = pr;
+    *out = pr.release();
     return QS_OK;
 }
 
@@ -644,61 +647,67 @@ int qs_plan_fusion(const qs_circuit *c, int n_qubits, int max_k, int *n_blocks, 
                    int *block_k, int *block_qubits)
 {
     clear_error();
-    if (n_qubits < 1 || n_qubits > 63) return fail(QS_EINVAL, "n_qubits=%d outside [1, 63]", n_qubits);
-    if (max_k < 1 || max_k > QS_MAX_K) return fail(QS_EINVAL, "max_k=%d outside [1, %d]", max_k, QS_MAX_K);
-    if (int rc = validate_circuit(c, n_qubits)) return rc;
-    if (!n_blocks || (c->n_gates && (!block_of_gate || !block_k || !block_qubits)))
-        return fail(QS_EINVAL, "NULL output arrays");
-    Plan p;
-    if (int rc = plan_fusion(n_qubits, c->n_gates, c->k, c->targets, c->ctrl_mask, max_k, p, far_qubit(16)))
-        return rc;
-    *n_blocks = int(p.block_gates.size());
-    for (int g = 0; g < c->n_gates; ++g) block_of_gate[g] = p.block_of_gate[size_t(g)];
-    for (size_t b = 0; b < p.block_gates.size(); ++b) {
-        const auto &q = p.block_qubits[b];
-        block_k[b] = int(q.size());
-        for (int i = 0; i < QS_MAX_K; ++i)
-            block_qubits[b * QS_MAX_K + size_t(i)] = i < int(q.size()) ? q[size_t(i)] : -1;
-    }
-    return QS_OK;
+    return guarded([&]() -> int {
+        if (n_qubits < 1 || n_qubits > 63) return fail(QS_EINVAL, "n_qubits=%d outside [1, 63]", n_qubits);
+        if (max_k < 1 || max_k > QS_MAX_K) return fail(QS_EINVAL, "max_k=%d outside [1, %d]", max_k, QS_MAX_K);
+        if (int rc = validate_circuit(c, n_qubits)) return rc;
+        if (!n_blocks || (c->n_gates && (!block_of_gate || !block_k || !block_qubits)))
+            return fail(QS_EINVAL, "NULL output arrays");
+        Plan p;
+        if (int rc = plan_fusion(n_qubits, c->n_gates, c->k, c->targets, c->ctrl_mask, max_k, p, far_qubit(16)))
+            return rc;
+        *n_blocks = int(p.block_gates.size());
+        for (int g = 0; g < c->n_gates; ++g) block_of_gate[g] = p.block_of_gate[size_t(g)];
+        for (size_t b = 0; b < p.block_gates.size(); ++b) {
+            const auto &q = p.block_qubits[b];
+            block_k[b] = int(q.size());
+            for (int i = 0; i < QS_MAX_K; ++i)
+                block_qubits[b * QS_MAX_K + size_t(i)] = i < int(q.size()) ? q[size_t(i)] : -1;
+        }
+        return QS_OK;
+    });
 }
 
 int qs_plan_passes(const qs_circuit *c, int n_qubits, int dtype, int max_k, qs_pass_plan *out)
 {
     clear_error();
-    if (!out) return fail(QS_EINVAL, "NULL output plan");
-    if (n_qubits < 1 || n_qubits > QS_MAX_QUBITS)
-        return fail(QS_EINVAL, "n_qubits=%d outside [1, %d]", n_qubits, QS_MAX_QUBITS);
-    if (dtype != QS_C64 && dtype != QS_C128) return fail(QS_EINVAL, "dtype=%d", dtype);
-    if (int rc = check_circuit(n_qubits, c, max_k)) return rc;
-    const size_t amp = dtype == QS_C128 ? 16 : 8;
-    Plan p;
-    if (int rc = plan_fusion(n_qubits, c->n_gates, c->k, c->targets, c->ctrl_mask, max_k, p, far_qubit(amp))) return rc;
-    *out = qs_pass_plan();
-    out->block_cost = blocks_cost(n_qubits, amp, c, p);
-    TilePlan t;
-    if (!plan_tiles(n_qubits, amp, c, true, INFINITY, t)) return QS_OK;
-    out->n_passes = int(t.passes.size());
-    out->n_stages = t.n_stages;
-    out->n_alone = int(t.steps.size() - t.passes.size());
-    std::copy_n(t.ops, 6, out->ops);
-    out->cost = t.cost;
-    const bool tiled = t.cost < out->block_cost;
-    out->program = tiled && program_by_passes(n_qubits);
-    out->circuit = tiled && (staged_by_passes(t) || out->program);
-    return QS_OK;
+    return guarded([&]() -> int {
+        if (!out) return fail(QS_EINVAL, "NULL output plan");
+        if (n_qubits < 1 || n_qubits > QS_MAX_QUBITS)
+            return fail(QS_EINVAL, "n_qubits=%d outside [1, %d]", n_qubits, QS_MAX_QUBITS);
+        if (dtype != QS_C64 && dtype != QS_C128) return fail(QS_EINVAL, "dtype=%d", dtype);
+        if (int rc = check_circuit(n_qubits, c, max_k)) return rc;
+        const size_t amp = dtype == QS_C128 ? 16 : 8;
+        Plan p;
+        if (int rc = plan_fusion(n_qubits, c->n_gates, c->k, c->targets, c->ctrl_mask, max_k, p, far_qubit(amp))) return rc;
+        *out = qs_pass_plan();
+        out->block_cost = blocks_cost(n_qubits, amp, c, p);
+        TilePlan t;
+        if (!plan_tiles(n_qubits, amp, c, true, INFINITY, t)) return QS_OK;
+        out->n_passes = int(t.passes.size());
+        out->n_stages = t.n_stages;
+        out->n_alone = int(t.steps.size() - t.passes.size());
+        std::copy_n(t.ops, 6, out->ops);
+        out->cost = t.cost;
+        const bool tiled = t.cost < out->block_cost;
+        out->program = tiled && program_by_passes(n_qubits);
+        out->circuit = tiled && (staged_by_passes(t) || out->program);
+        return QS_OK;
+    });
 }
 
 int qs_compile(qs_handle h, const qs_circuit *c, int max_k, qs_program *out)
 {
     clear_error();
-    if (int rc = check_handle(h)) return rc;
-    if (!out) return fail(QS_EINVAL, "NULL output program");
-    *out = nullptr;
-    if (int rc = check_circuit(h->n, c, max_k)) return rc;
-    Route r;
-    if (int rc = plan_route(h->n, h->amp_bytes(), c, max_k, false, r)) return rc;
-    return compile(h, c, r, out);
+    return guarded([&]() -> int {
+        if (int rc = check_handle(h)) return rc;
+        if (!out) return fail(QS_EINVAL, "NULL output program");
+        *out = nullptr;
+        if (int rc = check_circuit(h->n, c, max_k)) return rc;
+        Route r;
+        if (int rc = plan_route(h->n, h->amp_bytes(), c, max_k, false, r)) return rc;
+        return compile(h, c, r, out);
+    });
 }
 
 int qs_program_info(qs_program p, int *n_blocks, int *block_k, double *amp_moves_per_run)
@@ -770,38 +779,37 @@ int qs_program_free(qs_program p)
     clear_error();
     if (!p) return QS_OK;
     if (p->dmats || p->dmats32 || p->dwords) (void)hipDeviceSynchronize();
-    if (p->dwords) (void)hipFree(p->dwords);
-    if (p->dmats) (void)hipFree(p->dmats);
-    if (p->dmats32) (void)hipFree(p->dmats32);
-    delete p;
+    free_program(p);
     return QS_OK;
 }
 
 int qs_apply_circuit(qs_handle h, const qs_circuit *c, int max_k)
 {
     clear_error();
-    if (int rc = check_handle(h)) return rc;
-    if (int rc = check_circuit(h->n, c, max_k)) return rc;
-    // a replay would read whatever the staging ring holds by then
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(h->stream, &cap) != hipSuccess) (void)hipGetLastError();
-    if (cap != hipStreamCaptureStatusNone)
-        return fail(QS_EUNSUPPORTED, "qs_apply_circuit on a stream that is being captured: compile the circuit first");
-    Route r;
-    if (int rc = plan_route(h->n, h->amp_bytes(), c, max_k, true, r)) return rc;
-    if (r.tiled && staged_by_passes(r.tiles)) {
-        const TilePlan &t = r.tiles;
-        void *dw = nullptr;
-        if (int rc = h->stage.put(h->stream, t.words.data(), t.words.size() * sizeof(uint64_t), &dw)) return rc;
-        for (const TilePass &ps : t.passes)
-            if (int rc = launch_tile_pass(h, ps, static_cast<const uint64_t *>(dw))) return rc;
-        return QS_OK;
-    }
-    qs_program p = nullptr;
-    if (int rc = compile(h, c, r, &p)) return rc;
-    int rc = qs_run_program(h, p);
-    qs_program_free(p);
-    return rc;
+    return guarded([&]() -> int {
+        if (int rc = check_handle(h)) return rc;
+        if (int rc = check_circuit(h->n, c, max_k)) return rc;
+        // a replay would read whatever the staging ring holds by then
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(h->stream, &cap) != hipSuccess) (void)hipGetLastError();
+        if (cap != hipStreamCaptureStatusNone)
+            return fail(QS_EUNSUPPORTED, "qs_apply_circuit on a stream that is being captured: compile the circuit first");
+        Route r;
+        if (int rc = plan_route(h->n, h->amp_bytes(), c, max_k, true, r)) return rc;
+        if (r.tiled && staged_by_passes(r.tiles)) {
+            const TilePlan &t = r.tiles;
+            void *dw = nullptr;
+            if (int rc = h->stage.put(h->stream, t.words.data(), t.words.size() * sizeof(uint64_t), &dw)) return rc;
+            for (const TilePass &ps : t.passes)
+                if (int rc = launch_tile_pass(h, ps, static_cast<const uint64_t *>(dw))) return rc;
+            return QS_OK;
+        }
+        qs_program p = nullptr;
+        if (int rc = compile(h, c, r, &p)) return rc;
+        int rc = qs_run_program(h, p);
+        qs_program_free(p);
+        return rc;
+    });
 }
 
 int qs_norm2(qs_handle h, double *out)

@@ -914,5 +914,5 @@ extern "C" int qs_emulate_qft(qs_handle h, int q_lo, int m, int inverse)
     if (!h) return qs::fail(QS_EINVAL, "NULL handle");
     if (m < 1 || q_lo < 0 || q_lo + m > h->n)
         return qs::fail(QS_EINVAL, "QFT field [%d, %d) outside the %d-qubit state", q_lo, q_lo + m, h->n);
-    return qs::emulate_qft(h, q_lo, m, inverse);
+    return qs::guarded([&] { return qs::emulate_qft(h, q_lo, m, inverse); });
 }

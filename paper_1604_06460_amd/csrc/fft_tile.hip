@@ -25,7 +25,6 @@
 #include "fft_tile.h"
 
 #include <algorithm>
-#include <vector>
 
 #include "fft_dev.h"
 #include "tile_dev.h"
@@ -262,6 +261,19 @@ void launch_r(hipStream_t s, const void *src, void *dst, const Geom &g, int E, u
     }
 }
 
+// A few bit positions, on the stack: a launch between two passes allocates
+// nothing that could fail.
+struct Bits {
+    int v[64], n = 0;
+    void push_back(int b) { v[n++] = b; }
+    int size() const { return n; }
+    int *begin() { return v; }
+    int *end() { return v + n; }
+    const int *begin() const { return v; }
+    const int *end() const { return v + n; }
+    int operator[](int i) const { return v[i]; }
+};
+
 }  // namespace
 
 bool fft_tile_applies(int n, const fftdev::PassArgs &pa)
@@ -294,16 +306,16 @@ int launch_fft_tile(qs_state *h, const fftdev::PassArgs &pa, const void *src, vo
     if (pa.final_pass)
         for (int d = 0; d < pa.ndig; ++d)
             for (int i = 0; i < pa.dw[d]; ++i) dest[pa.dpos[d] + i] = pa.q_lo + pa.doff[d] + i;
-    std::vector<int> other;
+    Bits other, cols, rest;
     for (int q = 0; q < n; ++q)
         if (q < pa.dig_lo || q >= pa.dig_lo + r) other.push_back(q);
     std::sort(other.begin(), other.end(), [&](int a, int b) { return dest[a] < dest[b]; });
-    std::vector<int> cols(other.begin(), other.begin() + g.cb), rest(other.begin() + g.cb, other.end());
+    for (int i = 0; i < other.size(); ++i) (i < g.cb ? cols : rest).push_back(other[i]);
     std::sort(rest.begin(), rest.end());
-    g.nrest = int(rest.size());
+    g.nrest = rest.size();
     for (int i = 0; i < g.nrest; ++i) {
-        g.src[i] = uint8_t(rest[size_t(i)]);
-        g.dst[i] = uint8_t(dest[rest[size_t(i)]]);
+        g.src[i] = uint8_t(rest[i]);
+        g.dst[i] = uint8_t(dest[rest[i]]);
     }
     // Tile bit t < cb: column t. Tile bit cb + p: digit place p; after a step
     // over places [p, p + 4) these hold four bits of the output digit, whose
@@ -316,19 +328,19 @@ int launch_fft_tile(qs_state *h, const fftdev::PassArgs &pa, const void *src, vo
         }
         return 0;
     };
-    auto src_of = [&](int t) { return t < g.cb ? cols[size_t(t)] : pa.dig_lo + (t - g.cb); };
-    auto dst_of = [&](int t) { return t < g.cb ? dest[cols[size_t(t)]] : dest[pa.dig_lo + out_bit(t - g.cb)]; };
+    auto src_of = [&](int t) { return t < g.cb ? cols[t] : pa.dig_lo + (t - g.cb); };
+    auto dst_of = [&](int t) { return t < g.cb ? dest[cols[t]] : dest[pa.dig_lo + out_bit(t - g.cb)]; };
     // lay[i]: register tile bits regs (lowest first), thread bits ordered by
     // address inside a line, then so that the low five differ modulo 5 (LDS
     // banks), then by address
-    auto lay = [&](int i, const std::vector<int> &regs, auto &&addr) {
-        std::vector<int> thr, order;
+    auto lay = [&](int i, const Bits &regs, auto &&addr) {
+        Bits thr, order;
         for (int t = 0; t < E; ++t)
             if (std::find(regs.begin(), regs.end(), t) == regs.end()) thr.push_back(t);
         std::sort(thr.begin(), thr.end(), [&](int a, int b) { return addr(a) < addr(b); });
         uint32_t cls = 0;
         for (int t : thr) {
-            if (int(order.size()) >= 5) break;
+            if (order.size() >= 5) break;
             if (addr(t) < line || !((cls >> (t % 5)) & 1)) {
                 cls |= 1u << (t % 5);
                 order.push_back(t);
@@ -337,15 +349,15 @@ int launch_fft_tile(qs_state *h, const fftdev::PassArgs &pa, const void *src, vo
         for (int t : thr)
             if (std::find(order.begin(), order.end(), t) == order.end()) order.push_back(t);
         for (int k = 0; k < E - 4; ++k) {
-            g.lay[i][0] |= uint64_t(order[size_t(k)]) << (4 * k);
-            g.lay[i][1] |= uint64_t(addr(order[size_t(k)])) << (6 * k);
+            g.lay[i][0] |= uint64_t(order[k]) << (4 * k);
+            g.lay[i][1] |= uint64_t(addr(order[k])) << (6 * k);
         }
         for (int b = 0; b < 4; ++b) {
-            g.lay[i][0] |= uint64_t(regs[size_t(b)]) << (4 * (kMaxTile - 4 + b));
-            g.lay[i][2] |= uint64_t(addr(regs[size_t(b)])) << (6 * b);
+            g.lay[i][0] |= uint64_t(regs[b]) << (4 * (kMaxTile - 4 + b));
+            g.lay[i][2] |= uint64_t(addr(regs[b])) << (6 * b);
         }
     };
-    std::vector<int> top, mid, fin;
+    Bits top, mid, fin;
     if (steps == 1) {
         // columns fill the registers below the digit
         for (int t = E - 4; t < E; ++t) top.push_back(t);
@@ -363,7 +375,7 @@ int launch_fft_tile(qs_state *h, const fftdev::PassArgs &pa, const void *src, vo
         // the store keeps the load's thread bits: nothing is exchanged
         g.lay[2][0] = g.lay[0][0];
         for (int k = 0; k < E - 4; ++k) g.lay[2][1] |= uint64_t(dst_of(int(g.lay[0][0] >> (4 * k)) & 15)) << (6 * k);
-        for (int b = 0; b < 4; ++b) g.lay[2][2] |= uint64_t(dst_of(top[size_t(b)])) << (6 * b);
+        for (int b = 0; b < 4; ++b) g.lay[2][2] |= uint64_t(dst_of(top[b])) << (6 * b);
     } else {
         lay(2, fin, dst_of);
     }

@@ -5,6 +5,7 @@
 
 #include <cstdint>
 #include <cstdio>
+#include <exception>
 #include <string>
 #include <vector>
 
@@ -19,6 +20,18 @@ namespace qs {
 int fail(int status, const char *fmt, ...) __attribute__((format(printf, 2, 3)));
 void clear_error();
 int hip_fail(hipError_t e, const char *what);
+
+// Runs an entry point's body: nothing throws across the ABI, but host memory
+// may run out in the containers that planning fills.
+template <typename F>
+int guarded(F &&f)
+{
+    try {
+        return f();
+    } catch (const std::exception &) {
+        return fail(QS_ENOMEM, "host allocation failed");
+    }
+}
 
 #define QS_HIP(call)                                  \
     do {                                              \

@@ -153,3 +153,22 @@ def test_price_of_moves(Q, S):
 
     assert extra(S.g1(S.MAT_X, 9)) == pytest.approx(extra(S.Gate((9,), y)), rel=0.01)
     assert extra(S.swap(9, 11)) == pytest.approx(1.5 * extra(S.Gate((9,), y)), rel=0.01)
+
+
+def test_no_exception_leaves_the_library():
+    """Host memory that runs out while planning is QS_ENOMEM, not an abort."""
+    import subprocess
+    import sys
+    code = """
+import ctypes, resource
+from paper_1604_06460_amd import qs as Q
+from synth import circuits as S
+pc, plan, nb = Q.PackedCircuit([S.g1(S.MAT_H, 5)] * 200000), Q.PassPlan(), ctypes.c_int()
+out = [Q._ptr(__import__('numpy').zeros(200000 * k, dtype='int32')) for k in (1, 1, 6)]
+size = int(open('/proc/self/statm').read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (size + (1 << 19), size + (1 << 19)))
+print(Q.lib().qs_plan_passes(ctypes.byref(pc.c), 20, Q.QS_C128, 4, ctypes.byref(plan)),
+      Q.lib().qs_plan_fusion(ctypes.byref(pc.c), 20, 4, ctypes.byref(nb), *out), flush=True)
+"""
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout.split() == ["2", "2"], (r.returncode, r.stdout, r.stderr[-400:])
