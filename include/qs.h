@@ -611,8 +611,8 @@ int qs_apply_qpe_eig(qs_handle h, qs_unitary u, int ctrl_lo, int b);
  *     path 5 ignores it (one workgroup per tile).
  *   QS_TUNE_FFT_DIGIT (dtype, -, -, n bucket): largest FFT digit (bits per
  *     pass), 2..10.
- *   QS_TUNE_FFT_LDS_KB (dtype, -, -, n bucket): LDS tile budget of an FFT
- *     pass, 8..160 KiB (default 80: two workgroups per CU).
+ *   QS_TUNE_FFT_LDS_KB (dtype, -, -, n bucket): LDS tile budget of the
+ *     LDS-tile FFT passes, 8..160 KiB (default 80: two workgroups per CU).
  *   QS_TUNE_MFMA_WG_PER_CU (complex64, k = 5 or 6, -, n bucket): persistent grid
  *     of the matrix-core sweep in workgroups per compute unit, 1..16 (the
  *     pair-layout kernels cap it at the number that fit; default: that
@@ -622,18 +622,21 @@ int qs_apply_qpe_eig(qs_handle h, qs_unitary u, int ctrl_lo, int b);
  *     workgroup, 1..256.
  *   QS_TUNE_BATCH_BARRIER_AMPS (-, -, -, -): cost of a gang barrier, in
  *     amplitude-op units, used to order the batch queue.
- *   QS_TUNE_FFT_KERNEL (dtype, -, -, n bucket): FFT pass kernel. Passes
- *     with a 10-bit digit: 0 or 4 persistent workgroups holding a register
- *     tile of 128-byte rows and prefetching the next one (default), 3 one
- *     workgroup per register tile, 5 persistent register tiles with eight
- *     values per thread (1024-thread workgroups). Other passes, and every
- *     pass under 1 or 2: an LDS tile per workgroup (1), or persistent
- *     workgroups streaming LDS tiles (2). The register-tile kernels ignore
- *     the cache-policy option.
+ *   QS_TUNE_FFT_KERNEL (dtype, -, -, n bucket): FFT pass kernel. 0 or 4
+ *     (default): register tiles, for digits of any width on states of 10
+ *     qubits or more: one workgroup per tile, or, for most 10-bit digits,
+ *     persistent workgroups that prefetch the next tile of 128-byte rows. 3:
+ *     10-bit digits in one workgroup per register tile, 5 in persistent ones
+ *     with eight values per thread (1024-thread workgroups); their other
+ *     passes, and every pass under 1: an LDS tile per workgroup. 2: every
+ *     pass in persistent workgroups streaming LDS tiles. Passes that none of
+ *     these takes run as under 1. The register tiles read neither the LDS
+ *     budget nor the cache policy.
  *   QS_TUNE_SWEEP_NT (dtype, k, class, n bucket): cache policy of the
  *     register and LDS-staged dense sweeps: bit 0 nontemporal (streaming)
  *     stores, bit 1 nontemporal loads; 0 plain accesses.
- *   QS_TUNE_FFT_NT (dtype, -, -, n bucket): the same for the FFT passes.
+ *   QS_TUNE_FFT_NT (dtype, -, -, n bucket): the same for the LDS-tile FFT
+ *     passes.
  *   QS_TUNE_MODMUL_KERNEL (dtype, -, -, -): controlled modular
  *     multiplication with the work register at qubit 0: 0 or 5 the tiled
  *     gather with 64 x 128 tiles in 1024-thread workgroups (default), 4

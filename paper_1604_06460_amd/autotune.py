@@ -10,7 +10,8 @@ table that the binding applies at import (qs.TUNED_FILE):
     tiles), its cache policy and the grid cap in workgroups per CU, per
     (dtype, k, class of the lowest target, n bucket); each path is timed
     with plain and with streaming accesses and keeps its better time;
-  * FFT digit width and LDS tile budget per (dtype, n bucket);
+  * FFT pass kernel, digit width and, for the LDS-tile kernels, tile budget
+    and cache policy per (dtype, n bucket);
   * persistent grid of the matrix-core sweep (complex64, k = 6);
   * batch gang sizing and barrier cost.
 
@@ -158,32 +159,40 @@ def tune_sweep(timer, dtype, n, nb, reps, margin, log, rng):
 
 
 def tune_fft(timer, dtype, n, nb, reps, margin, log):
-    st = Q.State(n, dtype, stream=timer.stream.cuda_stream)
+    # two sizes of the bucket: n with digits of 10 bits, n - 2 with narrower
+    # ones (20 qubits complex64 alone would pick kernel 5, which takes twice
+    # the default's time on 18)
+    states = [Q.State(m, dtype, stream=timer.stream.cuda_stream) for m in (n, n - 2)]
+
+    def transforms():
+        return sum(timer.ms(lambda: st.emulate_qft(0, st.n), reps) for st in states)
+
     times = {}
-    # LDS-tile kernels over digit widths and tile budgets; the register-tile
-    # kernels (10-bit digits, their own LDS use) once each
+    # LDS-tile kernels over digit widths and tile budgets; the register tiles
+    # (their own LDS use) over digit widths, and those of 10 bits only once each
     cands = [(kern, digit, kb) for kern in (1, 2) for digit in (7, 8, 9, 10) for kb in (40, 80, 160)]
-    cands += [(kern, 10, 80) for kern in (3, 4, 5)]
+    cands += [(4, digit, 80) for digit in (7, 8, 9, 10)] + [(kern, 10, 80) for kern in (3, 5)]
     for kern, digit, kb in cands:
         Q.tune_set(Q.QS_TUNE_FFT_KERNEL, kern, dtype, 0, 0, nb)
         Q.tune_set(Q.QS_TUNE_FFT_DIGIT, digit, dtype, 0, 0, nb)
         Q.tune_set(Q.QS_TUNE_FFT_LDS_KB, kb, dtype, 0, 0, nb)
-        times[(kern, digit, kb)] = timer.ms(lambda: st.emulate_qft(0, n), reps)
-    st.free()
+        times[(kern, digit, kb)] = transforms()
     dflt = (4, 10, 80)
     best = _pick(times, dflt, margin)
     vals = best if best != dflt else (0, 0, 0)
     Q.tune_set(Q.QS_TUNE_FFT_KERNEL, vals[0], dtype, 0, 0, nb)
     Q.tune_set(Q.QS_TUNE_FFT_DIGIT, vals[1], dtype, 0, 0, nb)
     Q.tune_set(Q.QS_TUNE_FFT_LDS_KB, vals[2], dtype, 0, 0, nb)
-    st = Q.State(n, dtype, stream=timer.stream.cuda_stream)
     ntimes = {}
-    for ntv in (0, 1, 2, 3):
-        Q.tune_set(Q.QS_TUNE_FFT_NT, ntv, dtype, 0, 0, nb)
-        ntimes[ntv] = timer.ms(lambda: st.emulate_qft(0, n), reps)
-    st.free()
-    ntv = _pick(ntimes, 0, NT_MARGIN)
+    ntv = 0
+    if best[0] in (1, 2):           # the register tiles do not read it
+        for v in (0, 1, 2, 3):
+            Q.tune_set(Q.QS_TUNE_FFT_NT, v, dtype, 0, 0, nb)
+            ntimes[v] = transforms()
+        ntv = _pick(ntimes, 0, NT_MARGIN)
     Q.tune_set(Q.QS_TUNE_FFT_NT, ntv, dtype, 0, 0, nb)
+    for st in states:
+        st.free()
     log("fft %s n=%d: best kernel %d digit %d lds %d KiB (%.3f ms; default %.3f ms); nt %d %s" %
         (DT_NAME[dtype], n, best[0], best[1], best[2], times[best], times[dflt], ntv,
          {a: round(b, 3) for a, b in ntimes.items()}))

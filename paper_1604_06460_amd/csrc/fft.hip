@@ -834,8 +834,10 @@ int run_fft(qs_state *h, int q_lo, int m, int inverse)
         // 10-bit digits: the register-tile kernels, except where their columns
         // would be far apart (a digit that starts inside a 128-byte line: 26
         // qubits, digit at 0, complex64: 0.64 against 0.24 ms) and for large
-        // complex128 transforms (28 qubits: 5.81 against 5.51 ms; complex64
-        // 3.17 against 3.70)
+        // complex128 transforms (whole registers of 28, 29 and 30 qubits: 5.68,
+        // 11.9 and 23.7 against 5.46, 10.9 and 22.1 ms; fields of 20 qubits:
+        // 0.92 of the time at 26, 0.95 at 25, 1.05 at 23; complex64 1.04 to
+        // 1.35 of it from 22 qubits up)
         constexpr int line = sizeof(C2) == 16 ? 3 : 4;
         const bool tile = kern == 4 && fft_tile_applies(h->n, pa) &&
                           (pa.r != kRmax || pa.cb != reg_cb || (pa.dig_lo < line && !pa.final_pass) ||

@@ -112,6 +112,29 @@ def test_every_fft_shape_matches_oracle(Q, O, S, dtype):
 
 
 @pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("kern", [1, 2])
+def test_every_lds_tile_shape_matches_oracle(Q, O, S, dtype, kern):
+    """The LDS-tile kernels, which the budget and the cache policy are for,
+    over the digit widths: by default the register tiles take these passes."""
+    n = 15
+    psi0 = S.normal_state(n, 22)
+    Q.tune_set(Q.QS_TUNE_FFT_KERNEL, kern, dtype)
+    for q_lo, m in ((0, 15), (2, 11)):
+        ref = O.dft_numpy(psi0, q_lo, m, False)
+        for digit in (2, 4, 7, 10):
+            for kb, nt in ((8, 0), (64, 3), (160, 1)):
+                Q.tune_set(Q.QS_TUNE_FFT_DIGIT, digit, dtype)
+                Q.tune_set(Q.QS_TUNE_FFT_LDS_KB, kb, dtype)
+                Q.tune_set(Q.QS_TUNE_FFT_NT, nt, dtype)
+                st = Q.State(n, dtype)
+                st.set(psi0)
+                st.emulate_qft(q_lo, m)
+                got = st.get().astype(np.complex128)
+                st.free()
+                assert np.abs(got - ref).max() < TOL[dtype], (dtype, kern, q_lo, m, digit, kb)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
 def test_every_fft_kernel_matches_oracle(Q, O, S, dtype):
     """Every pass kernel the FFT option selects, on fields with 10-bit
     digits (the register-tile kernels) and without: forward and inverse,
