@@ -187,3 +187,92 @@ def test_capture(Q, S, dtype):
         assert np.array_equal(st.get().view(np.uint8), eager.view(np.uint8))
     prog.free()
     st.free()
+
+
+@pytest.mark.parametrize("dtype", [1, 0])
+@pytest.mark.parametrize("n", [10, 12, 14, 17])
+def test_general_one_qubit_matrices(Q, O, S, n, dtype):
+    """Matrices that are no rotation between phases (Y, a phased antidiagonal,
+    triangular ones, one of rank one), alone and controlled, on every qubit."""
+    rng = np.random.default_rng(n)
+    p = np.exp(2j * np.pi * rng.random(4))
+    kinds = [np.array([[0, -1j], [1j, 0]]), np.array([[0, p[0]], [p[1], 0]]), np.array([[1, 0.5 * p[2]], [0, p[3]]]),
+             np.array([[p[1], 0], [0.25, 1]]), np.array([[0.5, 0.5], [0.5, 0.5]])]
+    gates = [S.Gate((q,), _unitary(rng, 1)) for q in range(n)]
+    general = controlled = 0
+    for i, m in enumerate(kinds):
+        for q in range(n):
+            if i == 4 and q % 4:
+                continue                                  # keeps some of the norm
+            c = 1 << int(rng.integers(0, n))
+            if q % 3 == 0 and c != 1 << q:
+                gates.append(S.Gate((q,), m, c, c * int(rng.integers(0, 2))))
+                controlled += 1
+            else:
+                gates.append(S.Gate((q,), m))
+                general += i < 4
+    gates += S.random_layer_circuit(n, 1, seed=n)
+    plan = Q.plan_passes(gates, n, dtype, 4)
+    assert plan.circuit == 1 and plan.program == (n > 13)
+    assert plan.ops[0] >= general and plan.ops[1] == controlled
+    ref = O.apply_circuit(_psi(S, n, dtype).astype(np.complex128), gates)
+    for got in _runs(Q, S, n, dtype, gates):
+        assert _err(got, ref) < TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", [1, 0])
+@pytest.mark.parametrize("n", [14, 15, 16, 17])
+def test_gates_alone_between_passes(Q, O, S, n, dtype):
+    """Three-qubit gates and two-qubit gates under controls, which no pass
+    takes, between layers that passes do."""
+    rng = np.random.default_rng(20 + n)
+    gates = []
+    for i in range(4):
+        gates += S.random_layer_circuit(n, 3, seed=n + i)
+        q = [int(x) for x in rng.permutation(n)]
+        c = (1 << q[2]) | (1 << q[3])
+        gates += [S.Gate(tuple(q[4:7]), _unitary(rng, 3)), S.Gate((q[0], q[1]), _unitary(rng, 2), c, 1 << q[3])]
+    plan = Q.plan_passes(gates, n, dtype, 4)
+    assert plan.n_alone == 8 and plan.program == 1 and plan.circuit == 1
+    ref = O.apply_circuit(_psi(S, n, dtype).astype(np.complex128), gates)
+    for got in _runs(Q, S, n, dtype, gates):
+        assert _err(got, ref) < TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", [1, 0])
+def test_program_on_the_other_type(Q, O, S, dtype):
+    """A program has no type of its own: compiled on a state of one, its passes
+    (with a gate alone among them) run on states of both."""
+    n = 15
+    rng = np.random.default_rng(2)
+    gates = S.random_layer_circuit(n, 4, seed=5)
+    gates += [S.Gate((1, 4, 12), _unitary(rng, 3))] + S.random_layer_circuit(n, 4, seed=6)
+    maker = Q.State(n, dtype)
+    prog = maker.compile(gates, 4)
+    assert Q.plan_passes(gates, n, dtype, 4).program == 1
+    for other in (0, 1):
+        st = Q.State(n, other)
+        st.set(_psi(S, n, other))
+        st.run(prog)
+        ref = O.apply_circuit(_psi(S, n, other).astype(np.complex128), gates)
+        assert _err(st.get(), ref) < TOL[other]
+        st.free()
+    prog.free()
+    maker.free()
+
+
+def test_matrix_core_blocks_by_ranges(Q, O, S):
+    """6-qubit blocks of a complex64 program on the matrix cores: a run takes
+    passes there, block ranges take the blocks."""
+    n = 20
+    gates = S.random_layer_circuit(n, 8, seed=S.SEED_BASE + 3)
+    ref = O.apply_circuit(_psi(S, n, 0).astype(np.complex128), gates)
+    st = Q.State(n, 0)
+    st.set(_psi(S, n, 0))
+    prog = st.compile(gates, 6)
+    nb, ks, _ = prog.info()
+    assert max(ks) == 6
+    st.run_range(prog, 0, nb)
+    assert _err(st.get(), ref) < TOL[0]
+    prog.free()
+    st.free()
