@@ -47,53 +47,53 @@ __device__ __forceinline__ double as_double(uint64_t w) { return __longlong_as_d
 // multiply-add of each sum overwrites an input that nothing reads any more.
 // Written out, because every path through the operation loop has to leave
 // the tile in the same registers; from plain expressions the compiler makes
-// new values on each path, merges them by copies and spills.
+// new values on each path, merges them by copies and spills. CLS: the
+// matrix's register class, scalar or the thread's own.
+#define QS_PAIR(CLS)                                                                                      \
+    double ur, ui, vr, vi;                                                                                \
+    asm("v_mul_f64 %4, %8, %0\n\t"                                                                        \
+        "v_mul_f64 %5, %8, %1\n\t"                                                                        \
+        "v_mul_f64 %6, %12, %0\n\t"                                                                       \
+        "v_mul_f64 %7, %12, %1\n\t"                                                                       \
+        "v_fma_f64 %4, -%9, %1, %4\n\t"                                                                   \
+        "v_fma_f64 %5, %9, %0, %5\n\t"                                                                    \
+        "v_fma_f64 %6, -%13, %1, %6\n\t"                                                                  \
+        "v_fma_f64 %7, %13, %0, %7\n\t"                                                                   \
+        "v_fma_f64 %4, %10, %2, %4\n\t"                                                                   \
+        "v_fma_f64 %5, %10, %3, %5\n\t"                                                                   \
+        "v_fma_f64 %6, %14, %2, %6\n\t"                                                                   \
+        "v_fma_f64 %7, %15, %2, %7\n\t"                                                                   \
+        "v_fma_f64 %0, -%11, %3, %4\n\t"                                                                  \
+        "v_fma_f64 %1, %11, %2, %5\n\t"                                                                   \
+        "v_fma_f64 %2, -%15, %3, %6\n\t"                                                                  \
+        "v_fma_f64 %3, %14, %3, %7"                                                                       \
+        : "+v"(pr), "+v"(pi), "+v"(qr), "+v"(qi), "=&v"(ur), "=&v"(ui), "=&v"(vr), "=&v"(vi)              \
+        : CLS(m[0]), CLS(m[1]), CLS(m[2]), CLS(m[3]), CLS(m[4]), CLS(m[5]), CLS(m[6]), CLS(m[7]))
+
 __device__ __forceinline__ void pair(double &pr, double &pi, double &qr, double &qi, const double (&m)[8])
 {
-    double ur, ui, vr, vi;
-    asm("v_mul_f64 %4, %8, %0\n\t"
-        "v_mul_f64 %5, %8, %1\n\t"
-        "v_mul_f64 %6, %12, %0\n\t"
-        "v_mul_f64 %7, %12, %1\n\t"
-        "v_fma_f64 %4, -%9, %1, %4\n\t"
-        "v_fma_f64 %5, %9, %0, %5\n\t"
-        "v_fma_f64 %6, -%13, %1, %6\n\t"
-        "v_fma_f64 %7, %13, %0, %7\n\t"
-        "v_fma_f64 %4, %10, %2, %4\n\t"
-        "v_fma_f64 %5, %10, %3, %5\n\t"
-        "v_fma_f64 %6, %14, %2, %6\n\t"
-        "v_fma_f64 %7, %15, %2, %7\n\t"
-        "v_fma_f64 %0, -%11, %3, %4\n\t"
-        "v_fma_f64 %1, %11, %2, %5\n\t"
-        "v_fma_f64 %2, -%15, %3, %6\n\t"
-        "v_fma_f64 %3, %14, %3, %7"
-        : "+v"(pr), "+v"(pi), "+v"(qr), "+v"(qi), "=&v"(ur), "=&v"(ui), "=&v"(vr), "=&v"(vi)
-        : "s"(m[0]), "s"(m[1]), "s"(m[2]), "s"(m[3]), "s"(m[4]), "s"(m[5]), "s"(m[6]), "s"(m[7]));
+    QS_PAIR("s");
 }
 
-// Amplitude x times the thread's phase f, in place.
-__device__ __forceinline__ void phase(double &xr, double &xi, double fr, double fi)
+__device__ __forceinline__ void cpair(double &pr, double &pi, double &qr, double &qi, const double (&m)[8])
 {
-    double u, v;
-    asm("v_mul_f64 %2, %5, %1\n\t"
-        "v_mul_f64 %3, %5, %0\n\t"
-        "v_fma_f64 %0, %4, %0, -%2\n\t"
-        "v_fma_f64 %1, %4, %1, %3"
-        : "+v"(xr), "+v"(xi), "=&v"(u), "=&v"(v)
-        : "v"(fr), "v"(fi));
+    QS_PAIR("v");
 }
 
-// Amplitude x times a phase that all threads share, in place.
-__device__ __forceinline__ void uphase(double &xr, double &xi, double fr, double fi)
-{
-    double u, v;
-    asm("v_mul_f64 %2, %5, %1\n\t"
-        "v_mul_f64 %3, %5, %0\n\t"
-        "v_fma_f64 %0, %4, %0, -%2\n\t"
-        "v_fma_f64 %1, %4, %1, %3"
-        : "+v"(xr), "+v"(xi), "=&v"(u), "=&v"(v)
-        : "s"(fr), "s"(fi));
-}
+// Amplitude x times a phase f, in place: the thread's own, or (uphase) one
+// that all threads share.
+#define QS_PHASE(CLS)                                                                                     \
+    double u, v;                                                                                          \
+    asm("v_mul_f64 %2, %5, %1\n\t"                                                                        \
+        "v_mul_f64 %3, %5, %0\n\t"                                                                        \
+        "v_fma_f64 %0, %4, %0, -%2\n\t"                                                                   \
+        "v_fma_f64 %1, %4, %1, %3"                                                                        \
+        : "+v"(xr), "+v"(xi), "=&v"(u), "=&v"(v)                                                          \
+        : CLS(fr), CLS(fi))
+
+__device__ __forceinline__ void phase(double &xr, double &xi, double fr, double fi) { QS_PHASE("v"); }
+
+__device__ __forceinline__ void uphase(double &xr, double &xi, double fr, double fi) { QS_PHASE("s"); }
 
 // Flips the sign of x where the top bit of f is set: hi ^ (f & top).
 __device__ __forceinline__ void flip(double &x, uint32_t f, uint32_t top)
@@ -148,29 +148,6 @@ __device__ __forceinline__ void rotate1(double (&xr)[16], double (&xi)[16], cons
 // do, bit j of `amps` whether register j's do. A thread whose bits do not
 // match multiplies by the identity, exactly: a branch on `on` would make the
 // compiler copy the tile on every path around it.
-__device__ __forceinline__ void cpair(double &pr, double &pi, double &qr, double &qi, const double (&m)[8])
-{
-    double ur, ui, vr, vi;
-    asm("v_mul_f64 %4, %8, %0\n\t"
-        "v_mul_f64 %5, %8, %1\n\t"
-        "v_mul_f64 %6, %12, %0\n\t"
-        "v_mul_f64 %7, %12, %1\n\t"
-        "v_fma_f64 %4, -%9, %1, %4\n\t"
-        "v_fma_f64 %5, %9, %0, %5\n\t"
-        "v_fma_f64 %6, -%13, %1, %6\n\t"
-        "v_fma_f64 %7, %13, %0, %7\n\t"
-        "v_fma_f64 %4, %10, %2, %4\n\t"
-        "v_fma_f64 %5, %10, %3, %5\n\t"
-        "v_fma_f64 %6, %14, %2, %6\n\t"
-        "v_fma_f64 %7, %15, %2, %7\n\t"
-        "v_fma_f64 %0, -%11, %3, %4\n\t"
-        "v_fma_f64 %1, %11, %2, %5\n\t"
-        "v_fma_f64 %2, -%15, %3, %6\n\t"
-        "v_fma_f64 %3, %14, %3, %7"
-        : "+v"(pr), "+v"(pi), "+v"(qr), "+v"(qi), "=&v"(ur), "=&v"(ui), "=&v"(vr), "=&v"(vi)
-        : "v"(m[0]), "v"(m[1]), "v"(m[2]), "v"(m[3]), "v"(m[4]), "v"(m[5]), "v"(m[6]), "v"(m[7]));
-}
-
 template <int B>
 __device__ __forceinline__ void cdense1(double (&xr)[16], double (&xi)[16], Words w, bool on, uint32_t amps)
 {
