@@ -192,7 +192,8 @@ int qs_compile(qs_handle h, const qs_circuit *c, int max_k, qs_program *out);
 /* How the library would apply a circuit as passes over tiles of the state
  * (each pass reads and writes the state once and applies many gates), and
  * whether it would: qs_run_program and qs_apply_circuit compare the estimated
- * cost of the passes with that of the fused blocks. */
+ * time of the passes with that of the fused blocks, the latter with what
+ * planning and compiling take too. */
 typedef struct qs_pass_plan {
     int n_passes;        /* reads and writes of the whole state */
     int n_stages;        /* exchanges of register qubits, over all passes */
@@ -201,7 +202,7 @@ typedef struct qs_pass_plan {
                             same under controls, X, two-qubit, real
                             one-qubit, diagonal */
     double cost;         /* estimated time in microseconds */
-    double block_cost;   /* the same for the blocks */
+    double block_cost;   /* the same for the blocks, once composed */
     int program;         /* 1 if qs_run_program takes the passes */
     int circuit;         /* 1 if qs_apply_circuit takes them */
 } qs_pass_plan;

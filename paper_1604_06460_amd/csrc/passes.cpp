@@ -29,6 +29,18 @@ enum Kind { kOne, kRotation, kTwo, kSwap, kDiagonal, kAlone, kNothing };
 
 typedef std::complex<long double> Phase;
 
+// Products and quotients as they are: the operators look for infinities in
+// every one and scale every quotient, which took a third of the planning.
+Phase times(const Phase &a, const Phase &b)
+{
+    return Phase(a.real() * b.real() - a.imag() * b.imag(), a.real() * b.imag() + a.imag() * b.real());
+}
+Phase over(const Phase &a, const Phase &b)
+{
+    const long double n = b.real() * b.real() + b.imag() * b.imag();
+    return Phase((a.real() * b.real() + a.imag() * b.imag()) / n, (a.imag() * b.real() - a.real() * b.imag()) / n);
+}
+
 struct TGate {
     int kind = kAlone;
     bool x = false;            // kOne: exactly X
@@ -46,7 +58,7 @@ struct TGate {
 };
 
 struct Term {
-    uint64_t mask, vals;
+    uint64_t mask = 0, vals = 0;
     Phase p;
 };
 
@@ -90,7 +102,7 @@ bool as_controlled(const double *m, int &ctrl, int &val, double *u)
 // A unitary one-qubit gate as a real matrix (all but a rotation) between
 // phases. False where an entry is further from one than a few roundings of
 // its own (it may be any matrix, of any scale): of random unitaries, whose
-// entries have rounding errors of the whole matrix's size, 2 in 100. Every
+// entries have rounding errors of the whole matrix's size, 7 in 1000. Every
 // entry keeps its own modulus, so that what rounding left of the gate's norms
 // stays as given: over some hundred gates whose norms are off to the same
 // side it would add up.
@@ -105,12 +117,14 @@ bool as_rotation(TGate &g)
     }
     g.r[1] = -g.r[1];
     g.a0 = a[0];
-    g.after = a[2] / a[0];
+    g.after = over(a[2], a[0]);
     // the second column's phase, from both of its entries by their weight
-    const Phase b = a[3] / a[2] * (long double)(g.r[3] * g.r[3]) - a[1] / a[0] * (long double)(g.r[1] * g.r[1]);
-    g.before = b / std::abs(b);
-    return std::abs(a[0] * g.before * (long double)(g.r[1]) - u[1]) <= 1e-15L * std::abs(u[1]) &&
-           std::abs(a[2] * g.before * (long double)(g.r[3]) - u[3]) <= 1e-15L * std::abs(u[3]);
+    const Phase b = over(a[3], a[2]) * (long double)(g.r[3] * g.r[3]) - over(a[1], a[0]) * (long double)(g.r[1] * g.r[1]);
+    g.before = b / std::sqrt(std::norm(b));
+    auto near = [&](const Phase &p, int i) {
+        return std::norm(times(p, g.before) * (long double)(g.r[i]) - u[i]) <= 4e-30L * std::norm(u[i]);
+    };
+    return near(a[0], 1) && near(a[2], 3);
 }
 
 void read_gate(int k, const int *targets, const double *m, uint64_t cmask, uint64_t cvals, TGate &g)
@@ -239,7 +253,19 @@ struct Planner {
     int n, T, low;                 // low: qubits inside a 128-byte line
     const std::vector<TGate> &gates;
     TilePlan &out;
+    struct Placed {                // a phase as a stage sees it
+        uint32_t amps;
+        uint64_t om, ov;
+        Phase p;
+    };
     std::vector<Term> pending;     // phases not applied yet
+    std::vector<Term> now;         // scratch of flush
+    std::vector<Placed> sign, ph;
+    struct Inside {                // phases that depend on register bits alone, by register mask
+        uint32_t amps;
+        Phase p;
+    };
+    std::vector<Inside> inside;
     Phase scale = 1.0L;            // and the one that all amplitudes share
     double flops = 0;              // multiply-adds per amplitude
     mutable size_t seen = 0;       // where the last closure ended
@@ -353,15 +379,13 @@ struct Planner {
     // of both outside the registers is left in omask, ovals.
     static uint32_t registers(const int *reg_bit, uint64_t mask, uint64_t vals, uint64_t &omask, uint64_t &ovals)
     {
-        uint32_t amps = 0;
-        for (int j = 0; j < 16; ++j) {
-            bool on = true;
-            for (int b = 0; b < 4; ++b)
-                if ((mask >> reg_bit[b]) & 1) on = on && ((vals >> reg_bit[b]) & 1) == uint64_t((j >> b) & 1);
-            if (on) amps |= 1u << j;
-        }
+        static const uint32_t ones[4] = {0xaaaa, 0xcccc, 0xf0f0, 0xff00};   // registers j with bit b set
+        uint32_t amps = 0xffff;
         uint64_t r = 0;
-        for (int b = 0; b < 4; ++b) r |= 1ull << reg_bit[b];
+        for (int b = 0; b < 4; ++b) {
+            r |= 1ull << reg_bit[b];
+            if ((mask >> reg_bit[b]) & 1) amps &= (vals >> reg_bit[b]) & 1 ? ones[b] : ~ones[b];
+        }
         omask = mask & ~r;
         ovals = vals & ~r;
         return amps;
@@ -371,38 +395,42 @@ struct Planner {
     // every one, and the common phase.
     int flush(uint64_t which, bool all, const int *reg_bit, std::vector<uint64_t> &w)
     {
-        std::vector<Term> keep, now;
-        for (const Term &t : pending) (all || (t.mask & which) ? now : keep).push_back(t);
-        pending.swap(keep);
-        struct Placed {
-            uint32_t amps;
-            uint64_t om, ov;
-            Phase p;
+        now.clear();
+        sign.clear();
+        ph.clear();
+        size_t kept = 0;
+        for (size_t i = 0; i < pending.size(); ++i) {
+            if (all || (pending[i].mask & which)) now.push_back(pending[i]);
+            else pending[kept++] = pending[i];
+        }
+        pending.resize(kept);
+        inside.clear();
+        auto add_inside = [&](uint32_t amps, const Phase &f) {
+            for (Inside &i : inside)
+                if (i.amps == amps) {
+                    i.p = times(i.p, f);
+                    return;
+                }
+            inside.push_back(Inside{amps, f});
         };
-        std::vector<Placed> sign, ph;
-        Phase table[16];
-        std::vector<uint32_t> inside;    // register masks of the terms in the table
-        for (Phase &f : table) f = all ? scale : Phase(1.0L);
-        if (all && scale != Phase(1.0L)) inside.push_back(0xffff);
+        if (all && scale != Phase(1.0L)) add_inside(0xffff, scale);
         if (all) scale = 1.0L;
         for (const Term &t : now) {
             Placed q;
             q.amps = registers(reg_bit, t.mask, t.vals, q.om, q.ov);
             q.p = t.p;
             if (!q.om) {
-                for (int j = 0; j < 16; ++j)
-                    if ((q.amps >> j) & 1) table[j] *= t.p;
-                if (std::find(inside.begin(), inside.end(), q.amps) == inside.end()) inside.push_back(q.amps);
+                add_inside(q.amps, t.p);
             } else if (t.p == Phase(-1.0L) && sign.size() < 0xfff * kTileSigns) {
                 sign.push_back(q);
             } else {
                 ph.push_back(q);
             }
         }
-        std::stable_sort(ph.begin(), ph.end(), [](const Placed &a, const Placed &b) { return a.amps < b.amps; });
+        if (ph.size() > 1) std::stable_sort(ph.begin(), ph.end(), [](const Placed &a, const Placed &b) { return a.amps < b.amps; });
         // one set of registers: a group without conditions instead of a table
         const bool one = inside.size() == 1;
-        const uint32_t set = one ? inside[0] : 0;
+        const uint32_t set = one ? inside[0].amps : 0;
         const bool tab = inside.size() > 1;
         if (!one && !tab && sign.empty() && ph.empty()) return 0;
         const size_t head = w.size();
@@ -412,7 +440,12 @@ struct Planner {
             w.push_back(word_of(double(f.imag())));
         };
         if (tab) {
-            for (const Phase &f : table) put(f);
+            for (int j = 0; j < 16; ++j) {
+                Phase f = 1.0L;
+                for (const Inside &i : inside)
+                    if ((i.amps >> j) & 1) f = times(f, i.p);
+                put(f);
+            }
             flops += 4;
         }
         flops += sign.empty() ? 0.0 : 2.0 + 0.25 * double(sign.size());
@@ -431,7 +464,7 @@ struct Planner {
             while (!lone && e < ph.size() && ph[e].amps == amps) ++e;
             w.push_back(uint64_t(amps) | uint64_t(e - i) << 16);
             const bool first = one && amps == set;
-            put(first ? table[__builtin_ctz(set)] : Phase(1.0L));
+            put(first ? inside[0].p : Phase(1.0L));
             placed = placed || first;
             for (size_t j = i; j < e; ++j) {
                 w.push_back(ph[j].om);
@@ -587,7 +620,7 @@ struct Planner {
                     const TGate &g = gates[size_t(gi)];
                     ops += uint64_t(emit_gate(g, reg_bit, out.words));
                     if (g.kind != kRotation) continue;
-                    scale *= g.a0;
+                    scale = times(scale, g.a0);
                     if (g.after != Phase(1.0L)) pending.push_back(Term{g.need, g.need, g.after});
                 }
                 if (pending.size() > kWaiting) ops += uint64_t(flush(0, true, reg_bit, out.words));

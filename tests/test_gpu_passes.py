@@ -92,7 +92,6 @@ def test_long_circuits(Q, O, S):
 def test_one_call_plans_once(Q, S, n):
     """A long circuit that stays on blocks: one call takes no longer than
     compiling, running and freeing a program, which plans it once."""
-    import time
     rng = np.random.default_rng(6)
     wide = [S.Gate(tuple(int(x) for x in rng.permutation(n)[:3]), _unitary(rng, 3)) for _ in range(40)]
     layers = S.random_layer_circuit(n, 1400, seed=2)
@@ -100,7 +99,15 @@ def test_one_call_plans_once(Q, S, n):
     for i, g in enumerate(layers):
         gates += [g] if i % 6 else [g, wide[i % 40]]
     assert Q.plan_passes(gates, n, Q.QS_C128, 4).circuit == 0
-    st = Q.State(n, Q.QS_C128)
+    one, three = _one_and_three_calls(Q, n, Q.QS_C128, gates)
+    assert one < 1.1 * three
+
+
+def _one_and_three_calls(Q, n, dtype, gates):
+    """Time of one call, and of compiling, running and freeing: best of five,
+    each waited for."""
+    import time
+    st = Q.State(n, dtype)
     pc = Q.PackedCircuit(gates)
 
     def one_call():
@@ -123,8 +130,19 @@ def test_one_call_plans_once(Q, S, n):
             st.sync()
             best[fn] = min(best[fn], time.perf_counter() - t0)
     print("one call %.2f ms, compile, run and free %.2f ms" % (best[one_call] * 1e3, best[three_calls] * 1e3))
-    assert best[one_call] < 1.1 * best[three_calls]
     st.free()
+    return best[one_call], best[three_calls]
+
+
+@pytest.mark.parametrize("dtype", [1, 0])
+@pytest.mark.parametrize("n,layers,steps", [(12, 0, 1), (13, 64, 0), (14, 0, 8), (18, 32, 0)])
+def test_one_call_is_no_detour(Q, S, n, layers, steps, dtype):
+    """One call of a short, a long, a layered and an Ising circuit against
+    compiling and running its blocks: the choice is made on estimates that were
+    within 11 % of the better way, timing adds some."""
+    gates = S.random_layer_circuit(n, layers, seed=3) + S.tfim_trotter_step(n) * steps
+    one, three = _one_and_three_calls(Q, n, dtype, gates)
+    assert one < 1.35 * three
 
 
 @pytest.mark.parametrize("dtype", [1, 0])

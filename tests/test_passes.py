@@ -172,3 +172,12 @@ print(Q.lib().qs_plan_passes(ctypes.byref(pc.c), 20, Q.QS_C128, 4, ctypes.byref(
 """
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.split() == ["2", "2"], (r.returncode, r.stdout, r.stderr[-400:])
+
+
+def test_one_call_counts_what_compiling_takes(Q, S):
+    """An Ising step on 10 to 14 qubits: its blocks would run sooner than its
+    passes, were they there; composing them takes longer than both."""
+    for n in (10, 12, 14):
+        for k in (4, 6):
+            p = Q.plan_passes(S.tfim_trotter_step(n), n, Q.QS_C64, k)
+            assert p.circuit == 1 and p.program == 0, (n, k, p.cost, p.block_cost)
