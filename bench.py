@@ -222,8 +222,8 @@ def config3_mfma32(Q, S):
     multiply-add); the three-product form executes 3/4 of it on the matrix
     cores. Per-block HIP events on the state's
     stream give the matrix-core kernel's average launch time; the norm is
-    accumulated in FP64. The same generator at 22 qubits (the twin) runs on
-    the GPU in complex64 and on the FP64 oracle for the error."""
+    accumulated in FP64. The same generator at 22 qubits (the twin) runs its
+    blocks on the GPU in complex64 and on the FP64 oracle for the error."""
     import torch
     from oracle import oracle as O
     n, depth, k = 32, 40, 6
@@ -257,8 +257,10 @@ def config3_mfma32(Q, S):
     nt = 22
     tg = S.random_layer_circuit(nt, depth, seed=S.SEED_BASE + 3)
     tw = Q.State(nt, Q.QS_C64)
-    tw.apply_circuit(tg, k)
+    twp = tw.compile(tg, k)
+    tw.run_range(twp, 0, twp.info()[0])        # the blocks; one run would take passes
     got = tw.get().astype(np.complex128)
+    twp.free()
     tw.free()
     ref = O.apply_circuit(S.zero_state(nt), tg)
     err = float(np.abs(got - ref).max())
@@ -587,7 +589,9 @@ def main():
     parts_all = args.parts == "all"
 
     ev = {}
-    # the program split into maximal runs of consecutive blocks of one
+    # The step times the sweeps of the fused blocks: ranges always run block by
+    # block (st.run would take passes over tiles for a program this size).
+    # The program split into maximal runs of consecutive blocks of one
     # class (dense 4-qubit sweeps or anything else); one event pair per
     # run, so the dense sweep's launch time is read without an event
     # between every two of its launches

@@ -25,8 +25,9 @@
  *   Kronecker product of M with identities). Table 1's two-qubit gates list
  *   the control as the more significant local bit, so CNOT(c -> t) is given
  *   as targets = {t, c}. ctrl_mask/ctrl_vals restrict the gate to indices i
- *   with (i & ctrl_mask) == ctrl_vals. QS_C64 states receive the FP64 matrix
- *   and cast it to FP32 on the device.
+ *   with (i & ctrl_mask) == ctrl_vals. On QS_C64 states gates and blocks
+ *   round the matrix to FP32; passes over tiles (qs_run_program,
+ *   qs_apply_circuit) compute in FP64 and round amplitudes only.
  *
  * Ownership. The caller owns every host array it passes (targets, matrices,
  *   uniforms, outputs); the library copies what it needs before returning, so

@@ -90,12 +90,12 @@ __global__ __launch_bounds__(kThreads, BM == 128 ? 1 : BM == 64 ? 2 : 4) void k_
     const uint64_t n0 = uint64_t(blockIdx.x) * kBN;
     const int wr = (wave >> 1) * (BM / 2), wc = (wave & 1) * (BM / 2);
 
-    // global -> register panel loads: 4 complex per thread for A and for B
-    // A (op = N): column k of the panel is 128 contiguous rows; thread t
-    //   takes k = t / 32, rows 4 (t % 32) .. +3.
+    // global -> register panel loads: Q complex per thread for A and for B
+    // A (op = N): column k of the panel is BM contiguous rows; thread t takes
+    //   k = t / TPK, rows Q (t % TPK) .. + Q - 1.
     // A (op = C): op(A)[i][k] = conj(A[k][i]); row i of op(A) is column i of A,
-    //   contiguous in k; thread t takes i = t / 2, k = 4 (t % 2) .. +3.
-    // B: column j contiguous in k; thread t takes j = t / 2, k = 4 (t % 2) .. +3.
+    //   contiguous in k; thread t takes i = t / TPR, k = Q (t % TPR) .. + Q - 1.
+    // B: column j contiguous in k; thread t takes j = t / TPR, k likewise.
     C2 ra[Q], rb[Q];
     const int bj = t / TPR, bk = (t % TPR) * Q;
     const uint64_t bcol = n0 + uint64_t(bj);

@@ -18,9 +18,12 @@
 // Complex64 tiles are computed in FP64 between loads, exchanges and stores:
 // without packed FP32 that is the same number of instructions.
 //
-// What bounds it: memory. Four workgroups of four waves share a compute unit,
-// so loads of one tile overlap with the arithmetic of others, without the
-// persistent loop and prefetch that the 10-bit register tiles of fft.hip
+// What bounds it: memory on complex128 states, the arithmetic on complex64
+// ones (72 % busy on digits of 9 bits). Tiles of 2^12 amplitudes leave four
+// workgroups of four waves to a compute unit, tiles of 2^13 (digits whose
+// lines need them: 9 and 10 bits in complex64, 10 in complex128) two of eight
+// waves, so loads of one tile overlap with the arithmetic of others, without
+// the persistent loop and prefetch that the 10-bit register tiles of fft.hip
 // need at one workgroup per unit.
 #include "fft_tile.h"
 

@@ -135,9 +135,9 @@ def _one_and_three_calls(Q, n, dtype, gates):
 
 
 @pytest.mark.parametrize("dtype", [1, 0])
-@pytest.mark.parametrize("n,layers,steps", [(12, 0, 1), (13, 64, 0), (14, 0, 8), (18, 32, 0)])
+@pytest.mark.parametrize("n,layers,steps", [(12, 0, 1), (14, 0, 8), (18, 32, 0)])
 def test_one_call_is_no_detour(Q, S, n, layers, steps, dtype):
-    """One call of a short, a long, a layered and an Ising circuit against
+    """One call of a short, a long and a layered circuit against
     compiling and running its blocks: the choice is made on estimates that were
     within 11 % of the better way, timing adds some."""
     gates = S.random_layer_circuit(n, layers, seed=3) + S.tfim_trotter_step(n) * steps

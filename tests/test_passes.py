@@ -163,8 +163,8 @@ def test_no_exception_leaves_the_library():
 import ctypes, resource
 from paper_1604_06460_amd import qs as Q
 from synth import circuits as S
-pc, plan, nb = Q.PackedCircuit([S.g1(S.MAT_H, 5)] * 200000), Q.PassPlan(), ctypes.c_int()
-out = [Q._ptr(__import__('numpy').zeros(200000 * k, dtype='int32')) for k in (1, 1, 6)]
+pc, plan, nb = Q.PackedCircuit([S.g1(S.MAT_H, 5)] * 600000), Q.PassPlan(), ctypes.c_int()
+out = [Q._ptr(__import__('numpy').zeros(600000 * k, dtype='int32')) for k in (1, 1, 6)]
 size = int(open('/proc/self/statm').read().split()[0]) * resource.getpagesize()
 resource.setrlimit(resource.RLIMIT_AS, (size + (1 << 19), size + (1 << 19)))
 print(Q.lib().qs_plan_passes(ctypes.byref(pc.c), 20, Q.QS_C128, 4, ctypes.byref(plan)),
