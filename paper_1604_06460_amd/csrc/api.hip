@@ -250,15 +250,19 @@ int check_circuit(int n, const qs_circuit *c, int max_k)
     return QS_OK;
 }
 
-// Estimated time of a plan's blocks in microseconds.
-double blocks_cost(int n, size_t amp_bytes, const qs_circuit *c, const Plan &p)
+// Estimated time of a plan's blocks in microseconds, and of the gates that
+// passes would leave alone, each as a block.
+double blocks_cost(int n, size_t amp_bytes, const qs_circuit *c, const Plan &p, double &alone)
 {
     std::vector<char> diag(size_t(std::max(0, c->n_gates)));
     const double *m = c->matrices;
+    alone = 0;
     for (int g = 0; g < c->n_gates; ++g) {
         GateDesc d;
         classify(m, c->k[g], d);
         diag[size_t(g)] = d.cls == GC_IDENTITY || d.cls == GC_PHASE1 || d.cls == GC_DIAG;
+        const int ctrls = c->ctrl_mask ? __builtin_popcountll(c->ctrl_mask[g]) : 0;
+        if (!diag[size_t(g)] && c->k[g] >= (ctrls ? 2 : 3)) alone += dense_us(n, amp_bytes, c->k[g] + ctrls);
         m += size_t(2) << (2 * c->k[g]);
     }
     double cost = 0;
@@ -310,10 +314,13 @@ int plan_route(int n, size_t amp_bytes, const qs_circuit *c, int max_k, bool onc
 {
     if (int rc = plan_fusion(n, c->n_gates, c->k, c->targets, c->ctrl_mask, max_k, r.blocks, far_qubit(amp_bytes)))
         return rc;
-    r.block_cost = blocks_cost(n, amp_bytes, c, r.blocks);
     const bool program = program_by_passes(n);
+    if (!once && !program) return QS_OK;
+    double alone = 0;
+    r.block_cost = blocks_cost(n, amp_bytes, c, r.blocks, alone);
     const double limit = r.block_cost + (once ? compile_us(r.blocks, c->n_gates) - planning_us(c->n_gates) : 0.0);
-    r.tiled = (once || program) && plan_tiles(n, amp_bytes, c, program, limit, r.tiles);
+    // passes are not planned where the gates left alone rule them out
+    if ((program || alone == 0) && alone < limit) r.tiled = plan_tiles(n, amp_bytes, c, limit, r.tiles);
     return QS_OK;
 }
 
@@ -698,9 +705,10 @@ int qs_plan_passes(const qs_circuit *c, int n_qubits, int dtype, int max_k, qs_p
         Plan p;
         if (int rc = plan_fusion(n_qubits, c->n_gates, c->k, c->targets, c->ctrl_mask, max_k, p, far_qubit(amp))) return rc;
         *out = qs_pass_plan();
-        out->block_cost = blocks_cost(n_qubits, amp, c, p);
+        double alone = 0;
+        out->block_cost = blocks_cost(n_qubits, amp, c, p, alone);
         TilePlan t;
-        if (!plan_tiles(n_qubits, amp, c, true, INFINITY, t)) return QS_OK;
+        if (!plan_tiles(n_qubits, amp, c, INFINITY, t)) return QS_OK;
         out->n_passes = int(t.passes.size());
         out->n_stages = t.n_stages;
         out->n_alone = int(t.steps.size() - t.passes.size());

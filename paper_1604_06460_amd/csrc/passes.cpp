@@ -678,7 +678,7 @@ static double passes_us(int n, size_t amp_bytes, const TilePlan &p, double flops
            mem * (0.52 * double(p.passes.size()) + 0.79 * flops / fma);
 }
 
-bool plan_tiles(int n, size_t amp_bytes, const qs_circuit *c, bool alone, double limit, TilePlan &out)
+bool plan_tiles(int n, size_t amp_bytes, const qs_circuit *c, double limit, TilePlan &out)
 {
     out = TilePlan();
     if (n < kTileBitsMin) return false;
@@ -691,12 +691,14 @@ bool plan_tiles(int n, size_t amp_bytes, const qs_circuit *c, bool alone, double
     const int *tp = c->targets;
     const double *mp = c->matrices;
     GateList left;
+    double swept = 0;              // time of the gates left alone
     for (int g = 0; g < c->n_gates; ++g) {
         const uint64_t cm = c->ctrl_mask ? c->ctrl_mask[g] : 0;
         read_gate(c->k[g], tp, mp, cm, c->ctrl_vals ? c->ctrl_vals[g] & cm : 0, gates[size_t(g)]);
         tp += c->k[g];
         mp += size_t(2) << (2 * c->k[g]);
-        if (gates[size_t(g)].kind == kAlone && !alone) return false;
+        if (gates[size_t(g)].kind == kAlone)   // a block over its targets and controls
+            swept += dense_us(n, amp_bytes, bits(gates[size_t(g)].need | gates[size_t(g)].diag));
         if (gates[size_t(g)].kind != kNothing) left.add(g, gates[size_t(g)]);
     }
     Planner pl(n, T, low, gates, out);
@@ -705,7 +707,6 @@ bool plan_tiles(int n, size_t amp_bytes, const qs_circuit *c, bool alone, double
     // of one for each pass, and saves a fifth of the passes: worth it once a
     // pass takes as long.
     const bool search = (amp_bytes << n) >= (size_t(1) << 29);
-    double swept = 0;
     auto cost = [&]() { return passes_us(n, amp_bytes, out, pl.flops) + swept; };
     auto front_alone = [&]() { return !left.empty() && gates[size_t(left.ids[left.front])].kind == kAlone; };
     while (!left.empty()) {
@@ -713,8 +714,6 @@ bool plan_tiles(int n, size_t amp_bytes, const qs_circuit *c, bool alone, double
             TileStep s;
             s.gate = left.ids[left.front++];
             out.steps.push_back(s);
-            // a block over its targets and controls
-            swept += dense_us(n, amp_bytes, bits(gates[size_t(s.gate)].need | gates[size_t(s.gate)].diag));
             continue;
         }
         if (cost() >= limit) break;

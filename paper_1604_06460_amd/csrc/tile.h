@@ -64,10 +64,9 @@ struct TilePlan {
 double dense_us(int n, size_t amp_bytes, int k);
 double diagonal_us(int n, size_t amp_bytes);
 
-// False where no plan is made: states smaller than a tile, a gate of its own
-// where `alone` does not allow any, or a cost of `limit` or more (planning
-// stops there).
-bool plan_tiles(int n, size_t amp_bytes, const qs_circuit *c, bool alone, double limit, TilePlan &out);
+// False where no plan is made: states smaller than a tile, or a cost of
+// `limit` or more (planning stops there).
+bool plan_tiles(int n, size_t amp_bytes, const qs_circuit *c, double limit, TilePlan &out);
 
 int launch_tile_pass(qs_state *h, const TilePass &p, const uint64_t *dwords);
 
