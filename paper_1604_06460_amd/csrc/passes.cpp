@@ -119,7 +119,8 @@ bool as_rotation(TGate &g)
     g.a0 = a[0];
     g.after = over(a[2], a[0]);
     // the second column's phase, from both of its entries by their weight
-    const Phase b = over(a[3], a[2]) * (long double)(g.r[3] * g.r[3]) - over(a[1], a[0]) * (long double)(g.r[1] * g.r[1]);
+    const Phase b = over(a[3], a[2]) * (long double)(g.r[3] * g.r[3]) -
+                    over(a[1], a[0]) * (long double)(g.r[1] * g.r[1]);
     g.before = b / std::sqrt(std::norm(b));
     auto near = [&](const Phase &p, int i) {
         return std::norm(times(p, g.before) * (long double)(g.r[i]) - u[i]) <= 4e-30L * std::norm(u[i]);
@@ -428,7 +429,8 @@ struct Planner {
                 ph.push_back(q);
             }
         }
-        if (ph.size() > 1) std::stable_sort(ph.begin(), ph.end(), [](const Placed &a, const Placed &b) { return a.amps < b.amps; });
+        if (ph.size() > 1)
+            std::stable_sort(ph.begin(), ph.end(), [](const Placed &a, const Placed &b) { return a.amps < b.amps; });
         // one set of registers: a group without conditions instead of a table
         const bool one = inside.size() == 1;
         const uint32_t set = one ? inside[0].amps : 0;
